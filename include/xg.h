@@ -98,7 +98,12 @@ typedef struct {
                                in fp64 inside one program. */
 } xg_program_desc;
 
-/* Compilation and launch options.  Zero means "library default". */
+/* Compilation and launch options.  Zero means "library default".  With every
+ * launch option zero (block, ipt, chunk_ops, reg_budget, lds_slots, prefetch,
+ * waves, coop_phase) the library plans each mode twice, for launches that
+ * fill the chip and for launches of few 64-instance tiles, and each call runs
+ * the plan modelled faster for its n (programs with binary32 tags keep one
+ * plan).  A program rounds alike in all of its plans. */
 typedef struct {
   int32_t block;       /* threads per workgroup: 64, 128, 256 (default 64) */
   int32_t ipt;         /* instances per thread: 1, 2, 4 (default 1) */
@@ -188,14 +193,16 @@ xg_status xg_program_info(xg_program* p, int32_t mode, xg_info* info);
  * those of modes 1 and 2. */
 xg_status xg_program_options(xg_program* p, int32_t mode, xg_options* out);
 
-/* Device workspace (bytes) an evaluation of n instances needs: values that
- * cross kernel boundaries of a chunked program.  The caller allocates it
+/* Device workspace (bytes) an evaluation of up to n instances needs, in
+ * whichever of the library's plans runs it: values that cross kernel
+ * boundaries of a chunked program, and spills.  The caller allocates it
  * (e.g. as a torch tensor) and passes it to the evaluation; 0 means none is
  * needed and NULL may be passed. */
 xg_status xg_workspace_bytes(xg_program* p, int64_t n, int32_t mode, size_t* bytes);
 
 /* Compile (if not yet compiled) the kernels of `mode` for the current
- * device.  Optional: evaluation compiles on first use. */
+ * device, both plans' where the library chose them.  Optional: evaluation
+ * compiles on first use (a capturing stream runs what is loaded). */
 xg_status xg_compile(xg_program* p, int32_t mode);
 
 /* Generate and compile the code objects of `mode` into the on-disk cache

@@ -25,7 +25,7 @@ using namespace xg;
 
 namespace xg {
 
-xg_options defaults(const xg_options* o, int dtype) {
+xg_options defaults(const xg_options* o, int dtype, bool mixed) {
   xg_options d;
   std::memset(&d, 0, sizeof d);
   if (o) d = *o;
@@ -33,10 +33,18 @@ xg_options defaults(const xg_options* o, int dtype) {
   if (d.block <= 0) d.block = 64;
   if (d.ipt <= 0) d.ipt = 1;
   if (d.chunk_ops <= 0) d.chunk_ops = 20000;
+  // A caller that sets no launch option gets one wave per SIMD: all of its
+  // registers, a quarter of the CU's LDS per workgroup (pick_few has the
+  // plan for launches too small for that).  With the whole LDS for one
+  // workgroup three of the four SIMDs idle (the pendulum at 65,536
+  // instances: 151 us, 43 with a quarter and 224 values in registers).
+  const bool alone = !mixed && d.reg_budget <= 0 && d.lds_slots <= 0 && d.waves == 1 && d.block == 64 && d.ipt == 1;
   // 16-wave cooperative tiles put 4 waves on each SIMD: 128 registers each
   if (d.reg_budget <= 0) d.reg_budget = d.waves >= 16 ? (dtype == XG_F32 ? 96 : 48)
-                                                      : (dtype == XG_F32 ? 200 : 112);
+                                        : alone       ? (dtype == XG_F32 ? 333 : 224)
+                                                      : (dtype == XG_F32 ? kTuneRegs32 : kTuneRegs64);
   if (d.lds_slots < 0) d.lds_slots = 0;
+  if (alone) d.lds_slots = (int32_t)(kLdsSpillBytes / 4 / ((int64_t)64 * (dtype == XG_F32 ? 4 : 8)));
   // the plan allocates only the spill slots it needs, up to all 160 KiB
   if (d.lds_slots == 0)  // all of the 160 KiB but 512 B kept for the kernels' own variables
     d.lds_slots = (int32_t)(kLdsSpillBytes / ((int64_t)d.block * d.ipt * d.waves *
@@ -84,21 +92,56 @@ EmitOptions emit_options_of(const xg_options& o) {
   return eo;
 }
 
-bool plan_mode(xg_program* p, int mode, std::string& err) {
-  ModeState& M = p->m[mode];
+// Modelled time of a single-wave plan's tile, in the units of the phased
+// plan's: its operations, and what its spills issue.  (A third is added: one
+// wave has nothing to fill its waits with.  Measured alone: the quadcopter
+// step 27,000 units against 21,000 operations, the pendulum 16,000 against
+// 15,000, a 22 x 22 LDL^T solve 9,000 against 3,500.)
+static int64_t tile_cost(const ModeState& M) {
+  int64_t c = 0;
+  for (const Node& nd : M.g.nodes) c += op_cost(nd.op);
+  return (c + 2 * M.est.lds_ops + 4 * M.est.ws_ops) * 4 / 3;
+}
+
+bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
+  ModeState& M = mode_state(p, mode, few);
   if (M.planned) return true;
-  const xg_options& opt = mode_opt(p, mode);
+  xg_options opt = mode_opt(p, mode, few);
+  const int budget = opt.reg_budget;
   if (mode == 0) M.g = p->g;
   else M.g = adjoint(p->g, mode == 2, opt.adj_seg_ops, &M.recompute_ops, opt.adj_fanout);
   // outside strict mode, divisions by a shared divisor multiply by one
   // reciprocal (each saves the ~10-instruction IEEE division sequence)
   if (!opt.strict) share_reciprocals(M.g);
+  M.n_nodes = (int64_t)M.g.nodes.size();
+  M.n_ops = 0;
+  for (const Node& nd : M.g.nodes) M.n_ops += is_arith(nd.op);
+  if (!opt.strict && !mixed_precision(M.g)) {
+    fold_negations(M.g, mode == 0);
+    fuse_multiply_adds(M.g);
+  }
+  // The library's adjoint plans.  The compiler reorders a long block and needs
+  // temporaries beyond the plan, so a long adjoint gets fewer, longer kernels
+  // (states crossing a cut go through the workspace) and a short one the
+  // small budget that keeps it out of scratch.  Fused adjoint at 8,192 /
+  // 65,536 instances, binary64: 7 links (64,000 operations, 351 values live)
+  // 153 / 622 us with 112 values in kernels of 20,000 and the whole LDS,
+  // 170 / 374 with 186, 148 / 241 with 168 in kernels of 40,000, 156 / 323
+  // there with 130; 6 links (266 live) 89 / 190, 97 / 180 with 168 and
+  // 84 / 129 with 130 in kernels of 40,000; 5 links 51 / 92 and 70 / 155 with
+  // 168, 4 links 34 / 71 and 41 / 113 in one kernel.
+  const bool long_adjoint = mode != 0 && p->library_plan[mode] && M.n_ops > 2 * (int64_t)opt.chunk_ops;
   PlanOptions po;
-  po.chunk_ops = opt.chunk_ops;
+  po.chunk_ops = long_adjoint ? 2 * opt.chunk_ops : opt.chunk_ops;
   po.waves = mode == 0 ? opt.waves : 1;
   po.coop_phase = mode == 0 ? opt.coop_phase : 0;
-  // exchange slots may take up to half of the LDS; spill slots get the rest
-  po.xch_cap = kLdsSpillBytes / (64 * (M.g.dtype == XG_F32 ? 4 : 8)) / 2;
+  // exchange slots may take most of the LDS, spill slots what they leave: a
+  // wave of a tile holds few values of its own (the pendulum on 4 waves: 127
+  // live at most, 243 exchanged at once), and an exchange or spill through
+  // the workspace costs an L2 round trip
+  po.lds_slots = kLdsSpillBytes / (64 * (M.g.dtype == XG_F32 ? 4 : 8));
+  po.xch_cap = po.lds_slots * 7 / 8;
+  po.reg_budget = opt.reg_budget;
   try {
     M.plan = make_plan(M.g, po);
   } catch (const std::logic_error& e) {
@@ -107,6 +150,16 @@ bool plan_mode(xg_program* p, int mode, std::string& err) {
   }
   EmitOptions eo = emit_options_of(opt);
   eo.waves = M.plan.waves;
+  // A program that overflows any budget by far is planned with less of it:
+  // the compiler has to rotate values beyond 128 through accumulation
+  // registers, which only pays while it saves spills (a 48 x 48 LDL^T solve,
+  // 1,272 live values: 1,020 B of scratch per lane at 224, none at 160)
+  if (p->library_plan[mode] && mode == 0 && p->g.dtype != XG_F32 && M.plan.max_live > budget * 4 / 3)
+    eo.reg_budget = std::min(budget, 160);
+  if (mode != 0 && p->library_plan[mode]) {
+    if (p->g.dtype == XG_F32) eo.reg_budget = kTuneRegs32;
+    else eo.reg_budget = !long_adjoint ? kTuneRegs64 : M.plan.max_live > 300 ? 168 : 130;
+  }
   char prefix[64];
   std::snprintf(prefix, sizeof prefix, "xg_m%d", mode);
   if (M.plan.phased) M.srcs = emit_phased(M.g, M.plan, eo, prefix, &M.est);
@@ -116,20 +169,98 @@ bool plan_mode(xg_program* p, int mode, std::string& err) {
     std::fprintf(stderr,
                  "[xg] mode %d: %zu nodes, %lld ops, max live %lld, %zu chunks, ws %d+%d slots, "
                  "lds %d slots, %d spills, recompute %lld, waves %d, phases %d, depth %d, xch %d, est %lld\n",
-                 mode, M.g.nodes.size(), (long long)M.plan.n_ops, (long long)M.plan.max_live,
+                 mode, M.g.nodes.size(), (long long)M.n_ops, (long long)M.plan.max_live,
                  M.plan.chunks.size(), M.plan.n_ws, M.est.extra_ws, M.est.lds_slots, M.est.spills,
                  (long long)M.recompute_ops, M.plan.waves, M.plan.n_phases, M.plan.depth, M.plan.n_xch,
                  (long long)M.plan.coop_est);
+  M.cost = M.plan.phased ? M.plan.coop_est : tile_cost(M);
   M.planned = true;
   (void)err;
   return true;
 }
 
-// Drop a mode's plan and code.  Kernels of it may still be queued or
-// running (launches are asynchronous), so each device that holds its
-// modules is drained before they are unloaded.
-void reset_mode(xg_program* p, int mode) {
-  ModeState& M = p->m[mode];
+// Tiles past which only the other plan is considered: four single-wave tiles
+// per SIMD fill the chip either way, and a tile's own latency no longer counts.
+static const int64_t kCUs = 256, kFewTiles = 16 * kCUs;
+
+// Whether a launch of so many tiles is modelled faster on the plan for few.
+static bool few_faster(const xg_program* p, int mode, int64_t tiles) {
+  if (mode != 0) return tiles <= kCUs;
+  const ModeState &B = p->m[mode], &F = p->few[mode];
+  const int64_t es = B.g.dtype == XG_F32 ? 4 : 8;
+  // a CU holds as many phased tiles as its LDS and its four SIMDs allow, and
+  // up to four single-wave tiles; either kind runs in rounds, or as long as
+  // its workspace traffic takes at the 2,000 bytes per cycle that HBM gives
+  const int64_t lds = ((int64_t)F.plan.n_xch * 64 + (int64_t)F.est.lds_slots * 64 * F.plan.waves) * es;
+  const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(4 / F.plan.waves, lds ? 160 * 1024 / lds : 4));
+  auto time = [&](int64_t cost, int64_t slots, const ModeState& M) {
+    const int64_t rounds = (tiles + slots - 1) / slots;
+    return std::max(rounds * cost * 5, tiles * M.est.ws_ops * 64 * es / 2000);
+  };
+  // (250 units: the phased tile's first loads and its barriers' skew; a
+  // 13 x 13 LDL^T solve takes 5.9 us so, 5.1 on one wave)
+  return time(F.cost + 250, kCUs * per_cu, F) < time(B.cost, 4 * kCUs, B);
+}
+
+// The plan for few tiles.  Forward: a phased tile of 4 or 2 waves, whichever
+// is modelled faster, for programs long enough to split (100 operations: a
+// 60-operation solve takes 3.8 us either way, the launch itself) and short
+// enough to plan (60,000).  Adjoint, binary64: the whole LDS for one
+// workgroup's spills (the pendulum's fused adjoint at 8,192 instances: 142 us,
+// 148 with a quarter of it).
+static void form_few(xg_program* p, int mode) {
+  p->few_state[mode] = -1;
+  std::string err;
+  if (!plan_mode(p, mode, err)) return;
+  const ModeState& B = p->m[mode];
+  xg_options o = mode_opt(p, mode);
+  const int64_t es = B.g.dtype == XG_F32 ? 4 : 8;
+  if (mode != 0) {
+    if (es == 4 || (B.est.lds_ops == 0 && B.est.ws_ops == 0)) return;
+    o.lds_slots = (int32_t)(kLdsSpillBytes / (64 * es));
+    p->few_opt[mode] = o;
+    if (plan_mode(p, mode, err, true)) {
+      p->few_state[mode] = 1;
+      p->few_most[mode] = 64 * kCUs;
+    } else {
+      p->few[mode] = ModeState();
+    }
+    return;
+  }
+  if (B.n_ops < 100 || B.n_ops > 60000) return;
+  ModeState best;
+  xg_options best_o = o;
+  for (int W : {4, 2}) {
+    o.waves = W;
+    o.coop_phase = kAutoPhase;
+    o.lds_slots = (int32_t)(kLdsSpillBytes / (64 * W * es));
+    p->few[0] = ModeState();
+    p->few_opt[0] = o;
+    if (!plan_mode(p, 0, err, true)) continue;
+    if (!best.planned || p->few[0].plan.coop_est < best.plan.coop_est) {
+      best = std::move(p->few[0]);
+      best_o = o;
+      best_o.coop_phase = best.plan.phase_len;
+    }
+  }
+  p->few[0] = std::move(best);
+  if (!p->few[0].planned) return;
+  p->few_opt[0] = best_o;
+  p->few_state[0] = 1;
+  int64_t most = kFewTiles;
+  while (most > 0 && !few_faster(p, 0, most)) --most;
+  p->few_most[0] = 64 * most;
+}
+
+bool pick_few(xg_program* p, int mode, int64_t n) {
+  if (!p->library_plan[mode]) return false;
+  const int64_t tiles = (n + 63) / 64;
+  if (tiles > kFewTiles) return false;
+  if (p->few_state[mode] == 0) form_few(p, mode);
+  return p->few_state[mode] > 0 && few_faster(p, mode, tiles);
+}
+
+static void drop_code(ModeState& M) {
   bool loaded = false;
   for (auto& d : M.devs) loaded = loaded || !d.mods.empty();
   if (loaded) {  // no device call for code that was never loaded
@@ -145,6 +276,15 @@ void reset_mode(xg_program* p, int mode) {
   M = ModeState();
 }
 
+// Drop a mode's plans and code.  Kernels of it may still be queued or
+// running (launches are asynchronous), so each device that holds its
+// modules is drained before they are unloaded.
+void reset_mode(xg_program* p, int mode) {
+  drop_code(p->m[mode]);
+  drop_code(p->few[mode]);
+  p->few_state[mode] = 0;
+}
+
 void destroy_program(xg_program* p) {
   for (int m = 0; m < 3; ++m) reset_mode(p, m);  // drains devices that hold its code
   delete p;
@@ -154,10 +294,10 @@ void destroy_program(xg_program* p) {
 // (no device needed): registers, LDS and scratch must let a workgroup be
 // resident, and a cooperative tile's device functions must find the kernel
 // arguments where they read them.
-static bool check_mode_code(xg_program* p, int mode, std::string& err) {
-  ModeState& M = p->m[mode];
+static bool check_mode_code(xg_program* p, int mode, std::string& err, bool few) {
+  ModeState& M = mode_state(p, mode, few);
   if (M.checked) return true;
-  const int block = mode_opt(p, mode).block * M.plan.waves;
+  const int block = mode_opt(p, mode, few).block * M.plan.waves;
   for (size_t c = 0; c < M.cos.size(); ++c) {
     char name[64];
     std::snprintf(name, sizeof name, "xg_m%d_c%zu", mode, c);
@@ -174,12 +314,12 @@ static bool check_mode_code(xg_program* p, int mode, std::string& err) {
   return true;
 }
 
-bool build_code(xg_program* p, int mode, std::string& err, xg_status* code) {
+bool build_code(xg_program* p, int mode, std::string& err, xg_status* code, bool few) {
   xg_status dummy;
   if (!code) code = &dummy;
   *code = XG_EINVAL;
-  if (!plan_mode(p, mode, err)) return false;
-  ModeState& M = p->m[mode];
+  if (!plan_mode(p, mode, err, few)) return false;
+  ModeState& M = mode_state(p, mode, few);
   if (!M.compiled) {
     *code = XG_ECOMPILE;
     if (!compile_many(M.srcs, base_compile_options(mode_opt(p, mode).strict != 0), M.cos, err,
@@ -191,22 +331,22 @@ bool build_code(xg_program* p, int mode, std::string& err, xg_status* code) {
     M.compiled = true;
   }
   *code = XG_EUNSUPPORTED;
-  return check_mode_code(p, mode, err);
+  return check_mode_code(p, mode, err, few);
 }
 
-bool compile_mode(xg_program* p, int mode, std::string& err, xg_status* code) {
+bool compile_mode(xg_program* p, int mode, std::string& err, xg_status* code, bool few) {
   xg_status dummy;
   if (!code) code = &dummy;
-  if (!build_code(p, mode, err, code)) return false;
+  if (!build_code(p, mode, err, code, few)) return false;
   *code = XG_EDEVICE;
-  ModeState& M = p->m[mode];
+  ModeState& M = mode_state(p, mode, few);
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) { err = "hipGetDevice failed"; return false; }
   for (auto& d : M.devs) if (d.device == dev) return true;
   // every kernel must fit its launch (code the autotuner compiled outside
   // build_code is checked here): a workgroup whose waves need more
   // registers than their SIMDs hold cannot be dispatched at all
-  if (!check_mode_code(p, mode, err)) { *code = XG_EUNSUPPORTED; return false; }
+  if (!check_mode_code(p, mode, err, few)) { *code = XG_EUNSUPPORTED; return false; }
   DevMod dm;
   dm.device = dev;
   auto unload = [&]() { for (auto mod : dm.mods) (void)hipModuleUnload(mod); };
@@ -278,20 +418,28 @@ bool overlap(const std::vector<Range>& A, const std::vector<Range>& B) {
 xg_status launch_mode(xg_program* p, int mode, int64_t n, const std::vector<const void*>& in,
                       const std::vector<int64_t>& ldi, const std::vector<void*>& out,
                       const std::vector<int64_t>& ldo, void* ws, void* stream) {
-  ModeState& M = p->m[mode];
   std::string err;
+  bool few;
   {
     std::lock_guard<std::mutex> lk(p->mu);
     xg_status code = XG_OK;
-    if (!compile_mode(p, mode, err, &code)) {
+    few = pick_few(p, mode, n);
+    if (few && !devmod(p->few[mode]) && devmod(p->m[mode])) {
+      // modules are not loaded while a stream captures: what is loaded runs
+      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+      if (hipStreamIsCapturing((hipStream_t)stream, &cs) != hipSuccess) (void)hipGetLastError();
+      if (cs != hipStreamCaptureStatusNone) few = false;
+    }
+    if (!compile_mode(p, mode, err, &code, few)) {
       set_error(err);
       return code;
     }
   }
+  ModeState& M = mode_state(p, mode, few);
   const DevMod* dm = devmod(M);
   if (!dm) { set_error("module not loaded for current device"); return XG_EDEVICE; }
   if (M.ws_slots() > 0 && !ws) { set_error("this program needs a workspace (xg_workspace_bytes)"); return XG_EINVAL; }
-  const xg_options& opt = mode_opt(p, mode);
+  const xg_options& opt = mode_opt(p, mode, few);
   const int block = opt.block * M.plan.waves, ipt = opt.ipt;
   const int64_t per = (int64_t)opt.block * ipt;  // instances per workgroup
   const int64_t grid = (n + per - 1) / per;
@@ -374,7 +522,6 @@ xg_status eval_adjoint_loaded(xg_program* p, int64_t n, const void* const* d_in,
     for (size_t j = 0; j < nro; ++j)
       if (ri[i].lo < ro[j].hi && ro[j].lo < ri[i].hi) { set_error("an output overlaps an input"); return XG_EALIAS; }
   const int mode = d_out ? 2 : 1;
-  ModeState& M = p->m[mode];
   // the kernel handles are copied under the lock (another thread may load
   // the mode on another device meanwhile, which grows the module table)
   constexpr size_t kMaxKernels = 64;
@@ -384,7 +531,25 @@ xg_status eval_adjoint_loaded(xg_program* p, int64_t n, const void* const* d_in,
   int32_t slots = 0;
   {
     std::lock_guard<std::mutex> lk(p->mu);
-    const DevMod* dm = M.compiled ? devmod(M) : nullptr;
+    // of the mode's loaded plans the one that n picks, or the other where
+    // only that one's workspace fits the array
+    const DevMod* dm = nullptr;
+    bool few = p->few_state[mode] == 1 && pick_few(p, mode, n);
+    for (int k = 0; k < 2; ++k, few = !few) {
+      ModeState& T = mode_state(p, mode, few);
+      if (few && p->few_state[mode] != 1) continue;
+      const DevMod* d = T.compiled ? devmod(T) : nullptr;
+      if (!d) continue;
+      const xg_options& o = mode_opt(p, mode, few);
+      const bool fits = ws_bytes_of(n, T.ws_slots(), o.block, o.ipt, es) <= ws_cap;
+      if (dm && !fits) continue;
+      dm = d;
+      block = o.block * T.plan.waves;
+      ipt = o.ipt;
+      per = o.block * o.ipt;
+      slots = T.ws_slots();
+      if (fits) break;
+    }
     if (dm && dm->fns.size() > kMaxKernels) {
       set_error("more kernels per evaluation than this entry point launches (64)");
       return XG_EUNSUPPORTED;
@@ -398,11 +563,6 @@ xg_status eval_adjoint_loaded(xg_program* p, int64_t n, const void* const* d_in,
                           : "the adjoint (mode 1) is not loaded on this device: call xg_compile(p, 1) first");
       return XG_EINVAL;
     }
-    const xg_options& opt = mode_opt(p, mode);
-    block = opt.block * M.plan.waves;
-    ipt = opt.ipt;
-    per = opt.block * ipt;
-    slots = M.ws_slots();
   }
   const int64_t grid = (n + per - 1) / per;
   if (grid > INT32_MAX || (uint64_t)n * es > 0xffffffffull) {
@@ -457,7 +617,11 @@ xg_status xg_program_load(const xg_program_desc* desc, const xg_options* opts, x
   std::string err;
   try {
     if (!build_graph(*desc, p->g, err)) { set_error(err); return XG_EINVAL; }
-    p->opt = defaults(opts, desc->dtype);
+    const bool mixed = mixed_precision(p->g);
+    p->opt = defaults(opts, desc->dtype, mixed);
+    const bool lib = !mixed && (!opts || (opts->block <= 0 && opts->ipt <= 0 && opts->chunk_ops <= 0 && opts->reg_budget <= 0 &&
+                               opts->lds_slots <= 0 && opts->prefetch == 0 && opts->waves <= 0 && opts->coop_phase <= 0));
+    for (bool& l : p->library_plan) l = lib;
     if (!check_opts(p->opt, desc->dtype, err)) { set_error(err); return XG_EINVAL; }
     p->aopt = p->opt;
     if (p->opt.eager) {
@@ -505,8 +669,8 @@ xg_status xg_program_info(xg_program* p, int32_t mode, xg_info* info) {
   } catch (const std::exception& e) { set_error(e.what()); return XG_ENOMEM; }
   ModeState& M = p->m[mode];
   std::memset(info, 0, sizeof *info);
-  info->n_nodes = (int64_t)M.g.nodes.size();
-  info->n_ops = M.plan.n_ops;
+  info->n_nodes = M.n_nodes;
+  info->n_ops = M.n_ops;
   info->max_live = M.plan.max_live;
   info->n_chunks = (int32_t)M.srcs.size();  // kernels per evaluation
   info->n_ws_slots = M.ws_slots();
@@ -540,6 +704,12 @@ xg_status xg_workspace_bytes(xg_program* p, int64_t n, int32_t mode, size_t* byt
   } catch (const std::exception& e) { set_error(e.what()); return XG_ENOMEM; }
   ModeState& M = p->m[mode];
   *bytes = ws_bytes_of(n, M.ws_slots(), mode_opt(p, mode).block, mode_opt(p, mode).ipt, esize(M.g));
+  try {
+    // either plan may run them, and a workspace for n instances serves fewer
+    (void)pick_few(p, mode, 1);
+    if (p->few_state[mode] == 1)
+      *bytes = std::max(*bytes, ws_bytes_of(std::min(n, p->few_most[mode]), p->few[mode].ws_slots(), 64, 1, esize(M.g)));
+  } catch (const std::exception& e) { set_error(e.what()); return XG_ENOMEM; }
   return XG_OK;
 }
 
@@ -560,7 +730,19 @@ xg_status xg_compile(xg_program* p, int32_t mode) {
   std::lock_guard<std::mutex> lk(p->mu);
   try {
     xg_status code = XG_OK;
+    const bool few = pick_few(p, mode, 1);  // the plan of the smallest launches too
+    if (few) {  // both plans' sources compile at once
+      std::vector<std::string> srcs = p->m[mode].srcs;
+      srcs.insert(srcs.end(), p->few[mode].srcs.begin(), p->few[mode].srcs.end());
+      std::vector<CodeObject> cos;
+      if (!compile_many(srcs, base_compile_options(mode_opt(p, mode).strict != 0), cos, err,
+                        mode_opt(p, mode).verbose != 0)) {
+        set_error(err);
+        return XG_ECOMPILE;
+      }
+    }
     if (!compile_mode(p, mode, err, &code)) { set_error(err); return code; }
+    if (few && !compile_mode(p, mode, err, &code, true)) { set_error(err); return code; }
   } catch (const std::exception& e) { set_error(e.what()); return XG_ENOMEM; }
   return XG_OK;
 }

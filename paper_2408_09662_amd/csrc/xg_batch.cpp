@@ -126,6 +126,7 @@ std::string build_batch_source(xg_batch* b, std::string& err) {
     for (size_t a = 0; a < g.nnz_out.size(); ++a)
       pro << "  T* __restrict__ out" << a << " = A.out" << a << "; const long long ldo" << a
           << " = A.ldo" << a << ";\n";
+    s << contract_pragma(b->progs[0]->opt.strict != 0) << contract_end(b->progs[0]->opt.strict != 0, g);
     s << "namespace P" << k << " {\n";
     if (M.plan.phased) {
       eo.waves = M.plan.waves;
@@ -286,7 +287,7 @@ xg_status batch_launch(xg_batch* b, const xg_batch_args* args, void* ws, void* s
 // ------------------------------------------------------------ autotune
 // Planner/emitter generation: part of every tuning-cache key, so decisions
 // timed on code an earlier generator emitted are not reused.
-constexpr uint64_t kTuneVersion = 4;
+constexpr uint64_t kTuneVersion = 5;
 
 // Key of a program for the tuning caches: its graph (per-instruction
 // binary32 tags included: a mixed-precision program is timed on its own
@@ -329,10 +330,14 @@ std::string tune_path(const xg_program* p, int64_t n, int mode) {
 // leaf lengths and fan-outs at three register budgets; for the forward,
 // cooperative tiles (level-split for wide programs with few tiles, phased
 // for narrow ones, 2-wave phased also at one tile per SIMD or more).
-std::vector<xg_options> tune_candidates(const xg_program* p, int64_t n, int mode) {
-  const xg_options base = mode_opt(p, mode);
+std::vector<xg_options> tune_candidates(xg_program* p, int64_t n, int mode) {
+  xg_options base = mode_opt(p, mode);
   const int64_t es = p->g.dtype == XG_F32 ? 4 : 8;
   const int64_t kCUs = 256, kSIMDs = 1024;
+  if (p->library_plan[mode]) {
+    base.reg_budget = p->g.dtype == XG_F32 ? kTuneRegs32 : kTuneRegs64;
+    base.lds_slots = (int32_t)(kLdsSpillBytes / (64 * es));
+  }
   auto lds_fit = [&](int32_t block, int32_t ipt) {
     const int64_t per = (int64_t)block * ipt;
     const int64_t wgs = (n + per - 1) / per;
@@ -348,6 +353,13 @@ std::vector<xg_options> tune_candidates(const xg_program* p, int64_t n, int mode
   if (fit < full) ldss.push_back(fit);
   std::vector<xg_options> cands;
   const int rb0 = base.reg_budget;
+  {  // what runs untuned (forward; the adjoint's candidates keep smaller workspaces)
+    std::lock_guard<std::mutex> lk(p->mu);
+    if (mode == 0 && p->library_plan[0]) {
+      cands.push_back(mode_opt(p, mode));
+      if (pick_few(p, mode, n)) cands.push_back(mode_opt(p, mode, true));
+    }
+  }
   for (int64_t l : ldss)
     for (int rb : {rb0 * 3 / 4, rb0, rb0 * 4 / 3, rb0 * 5 / 3, rb0 * 2, rb0 * 16 / 7, rb0 * 5 / 2})
       for (int pf : {24, 64}) {
@@ -673,7 +685,8 @@ xg_status xg_graph_capture_eval(xg_program* p, int64_t n, const void* const* d_i
     std::string err;
     std::lock_guard<std::mutex> lk(p->mu);
     xg_status code = XG_OK;
-    if (!compile_mode(p, 0, err, &code)) { set_error(err); return code; }  // no module loads while capturing
+    // no module loads while capturing
+    if (!compile_mode(p, 0, err, &code, pick_few(p, 0, n))) { set_error(err); return code; }
   }
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
@@ -708,7 +721,8 @@ xg_status xg_graph_capture_rollout(xg_program* p, int64_t n, int32_t steps, void
     std::string err;
     std::lock_guard<std::mutex> lk(p->mu);
     xg_status code = XG_OK;
-    if (!compile_mode(p, 0, err, &code)) { set_error(err); return code; }  // no module loads while capturing
+    // no module loads while capturing
+    if (!compile_mode(p, 0, err, &code, pick_few(p, 0, n))) { set_error(err); return code; }
   }
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
@@ -847,10 +861,12 @@ xg_status tune_mode(xg_program* p, int64_t n, int mode, size_t workspace_bytes, 
     if (mode == 0) {
       reset_mode(p, 0);
       p->opt = o;
+      p->library_plan[0] = false;
     } else {
       reset_mode(p, 1);
       reset_mode(p, 2);
       p->aopt = o;
+      p->library_plan[1] = p->library_plan[2] = false;
     }
     return true;
   };

@@ -258,7 +258,7 @@ std::string math_wrappers(bool f32, const Graph& g, bool inline_math) {
   // instructions of an f64 program.  The inline helpers are emitted only
   // for the operations the program has (other programs' sources, and so
   // their cached code, stay as they are).
-  bool has[XG_OP_COUNT] = {false};
+  bool has[kOpEnd] = {false};
   bool has_f32_trig = false;  // binary32-tagged SIN/COS in an f64 program
   int64_t n_inl = 0;
   for (const Node& nd : g.nodes) {
@@ -324,6 +324,14 @@ std::string expr(int op, const std::string& A, const std::string& B, const char*
   return std::string();
 }
 
+// A fused multiply-add, written out: what the compiler may contract by itself
+// depends on what else a kernel holds.
+std::string fma_expr(int op, const std::string& A, const std::string& B, const std::string& C, bool f32) {
+  const std::string f = f32 ? "__builtin_fmaf(" : "__builtin_fma(";
+  if (op == kOpFnma) return f + "-" + A + ", " + B + ", " + C + ")";
+  return f + A + ", " + B + ", " + (op == kOpFms ? "-" : "") + C + ")";
+}
+
 struct ChunkEmitter {
   const Graph& g;
   const Plan& pl;
@@ -356,7 +364,7 @@ struct ChunkEmitter {
       : g(g_), pl(pl_), eo(eo_), c(c_), extra_base(xb) {
     f32 = g.dtype == XG_F32;
     ipt = std::max(1, eo.ipt);
-    R = std::max(4, eo.reg_budget / ipt);
+    R = std::max(5, eo.reg_budget / ipt);
     lds_cap = std::max(0, eo.lds_slots / ipt);
   }
 
@@ -391,6 +399,7 @@ struct ChunkEmitter {
   std::string lds_at(int32_t slot, int r) {
     const int64_t off = (int64_t)(slot * ipt + r) * eo.block * (f32 ? 4 : 8);
     lds_hi = std::max(lds_hi, off);
+    st.lds_ops++;
     return "xg_lb" + std::to_string(off >> 16) + ", " + std::to_string(off & 0xffff) + "u";
   }
   // workspace element (slot, sub-instance r) of this lane: the block's
@@ -398,8 +407,12 @@ struct ChunkEmitter {
   std::string ws_off(int32_t slot, int r) const {
     return std::to_string((int64_t)(slot * ipt + r) * eo.block * (f32 ? 4 : 8)) + "u";
   }
-  std::string wld(int32_t slot, int r) const { return "xg_wld(wsr, " + ws_off(slot, r) + ", tidb)"; }
-  std::string wst(int32_t slot, int r, const std::string& v) const {
+  std::string wld(int32_t slot, int r) {
+    st.ws_ops++;
+    return "xg_wld(wsr, " + ws_off(slot, r) + ", tidb)";
+  }
+  std::string wst(int32_t slot, int r, const std::string& v) {
+    st.ws_ops++;
     return "xg_wst(wsr, " + ws_off(slot, r) + ", tidb, " + v + ");";
   }
   std::string gld(const std::string& base, const std::string& ld, int64_t e, int r) const {
@@ -438,6 +451,7 @@ struct ChunkEmitter {
   std::string xch_at(int32_t v) {  // as lds_at, in the exchange area (xg_xb0, ...)
     const int64_t off = (int64_t)pl.xch_slot[v] * 64 * (f32 ? 4 : 8);
     xch_hi = std::max(xch_hi, off);
+    st.lds_ops++;
     return "xg_xb" + std::to_string(off >> 16) + ", " + std::to_string(off & 0xffff) + "u";
   }
 
@@ -447,14 +461,14 @@ struct ChunkEmitter {
     return g.nodes[v].op != XG_OP_INPUT && (chunk_def[v] == c || pl.phased);
   }
 
-  void evict_one(int32_t protect_a, int32_t protect_b) {
+  void evict_one(int32_t protect_a, int32_t protect_b, int32_t protect_c) {
     std::vector<std::pair<int32_t, int32_t>> held;
     while (!heap.empty()) {
       auto e = heap.top();
       heap.pop();
       int32_t v = e.second;
       if (!inreg[v] || nextuse(v) != e.first) continue;  // stale
-      if (v == protect_a || v == protect_b) { held.push_back(e); continue; }
+      if (v == protect_a || v == protect_b || v == protect_c) { held.push_back(e); continue; }
       // victim v.  A value whose only other copy is in global memory (an
       // input, or a value the workspace holds) also moves to LDS while LDS
       // has room: its reloads then cost LDS latency instead of L2 latency.
@@ -503,10 +517,10 @@ struct ChunkEmitter {
     return kInf;
   }
 
-  void add_reg(int32_t v, int32_t pa, int32_t pb) {
+  void add_reg(int32_t v, int32_t pa, int32_t pb, int32_t pc = -1) {
     while (nreg >= R) {
       int before = nreg;
-      evict_one(pa, pb);
+      evict_one(pa, pb, pc);
       if (nreg == before) break;  // nothing evictable
     }
     inreg[v] = 1;
@@ -515,7 +529,7 @@ struct ChunkEmitter {
   }
 
   // bring v into registers (new materialisation)
-  void materialize(int32_t v, int32_t pa, int32_t pb) {
+  void materialize(int32_t v, int32_t pa, int32_t pb, int32_t pc = -1) {
     const Node& nd = g.nodes[v];
     nver[v]++;
     const bool from_xch = xch_home(v);
@@ -540,7 +554,7 @@ struct ChunkEmitter {
              wld(extra_base + xws_slot[v], r) + ";");
       }
     }
-    add_reg(v, pa, pb);
+    add_reg(v, pa, pb, pc);
   }
 
   void release(int32_t v) {  // after its last use in this chunk
@@ -589,9 +603,10 @@ struct ChunkEmitter {
     const Chunk& ch = pl.chunks[c];
     for (int32_t p = ch.begin; p < ch.end; ++p) {
       const Node& nd = g.nodes[pl.order[p]];
-      int32_t a = nd.a, b = nd.b;
+      int32_t a = nd.a, b = nd.b, d = nd.c;
       if (a >= 0 && g.nodes[a].op != XG_OP_CONST) uses[a].push_back(p);
       if (b >= 0 && b != a && g.nodes[b].op != XG_OP_CONST) uses[b].push_back(p);
+      if (d >= 0 && d != a && d != b && g.nodes[d].op != XG_OP_CONST) uses[d].push_back(p);
     }
     if (c == 0) {  // outputs that are constants
       for (int32_t v = 0; v < n; ++v)
@@ -612,6 +627,7 @@ struct ChunkEmitter {
       }
       int32_t a = (nd.a >= 0 && g.nodes[nd.a].op != XG_OP_CONST) ? nd.a : -1;
       int32_t b = (nd.b >= 0 && g.nodes[nd.b].op != XG_OP_CONST) ? nd.b : -1;
+      int32_t d = (nd.c >= 0 && g.nodes[nd.c].op != XG_OP_CONST) ? nd.c : -1;
       // issue now the reloads needed `prefetch` positions ahead (LDS
       // latency) and the global-memory reloads (inputs and workspace values
       // not held in LDS) needed four times as far ahead, so their latency
@@ -620,7 +636,7 @@ struct ChunkEmitter {
         const int32_t dist = far ? 4 * eo.prefetch : eo.prefetch;
         if (p + dist >= ch.end) continue;
         const Node& fn_ = g.nodes[pl.order[p + dist]];
-        for (int32_t o : {fn_.a, fn_.b}) {
+        for (int32_t o : {fn_.a, fn_.b, fn_.c}) {
           if (o < 0 || g.nodes[o].op == XG_OP_CONST || inreg[o]) continue;
           if (g.nodes[o].op != XG_OP_INPUT && chunk_def[o] == c && !defined[o])
             continue;  // not yet computed (defined between here and its use)
@@ -629,18 +645,20 @@ struct ChunkEmitter {
             continue;  // another wave's value: readable after its phase's barrier
           if (far && (lds_slot[o] >= 0 || xch_home(o))) continue;  // an LDS reload: the near distance covers it
           if (nreg >= R && farthest_next() <= p + dist) continue;  // would evict sooner uses
-          materialize(o, a, b);
+          materialize(o, a, b, d);
         }
       }
-      if (a >= 0 && !inreg[a]) materialize(a, a, b);
-      if (b >= 0 && b != a && !inreg[b]) materialize(b, a, b);
+      if (a >= 0 && !inreg[a]) materialize(a, a, b, d);
+      if (b >= 0 && b != a && !inreg[b]) materialize(b, a, b, d);
+      if (d >= 0 && d != a && d != b && !inreg[d]) materialize(d, a, b, d);
       nver[v]++;
       defined[v] = 1;
       const bool nf = nd.f32 != 0;  // binary32 instruction in an f64 program
       for (int r = 0; r < ipt; ++r) {
         std::string A = nd.a >= 0 ? operand(nd.a, r, nf) : "";
         std::string B = nd.b >= 0 ? operand(nd.b, r, nf) : "";
-        std::string e = expr(nd.op, A, B, ctype(v));
+        std::string e = is_fma(nd.op) ? fma_expr(nd.op, A, B, operand(nd.c, r, nf), f32 || nf)
+                                      : expr(nd.op, A, B, ctype(v));
         if (e.empty()) {
           std::string f = (eo.call_math && outlined(nd.op))
                               ? std::string("xg_") + op_name(nd.op) + (nf ? "f" : "")
@@ -651,7 +669,8 @@ struct ChunkEmitter {
       }
       // operands: advance past this use
       const int32_t b2 = (b == a) ? -1 : b;
-      for (int32_t o : {a, b2}) {
+      const int32_t d2 = (d == a || d == b) ? -1 : d;
+      for (int32_t o : {a, b2, d2}) {
         if (o < 0) continue;
         uptr[o]++;
         if (nextuse(o) == kInf) release(o);
@@ -662,7 +681,7 @@ struct ChunkEmitter {
         for (int r = 0; r < ipt; ++r) line(wst(pl.ws_slot[v], r, name(v, r)));
       if (pl.phased && pl.xch_slot[v] >= 0)
         line("xg_lds_st(" + xch_at(v) + ", " + name(v, 0) + ");");
-      if (nextuse(v) != kInf) add_reg(v, a, b);
+      if (nextuse(v) != kInf) add_reg(v, a, b, d);
     }
     if (pl.phased) enter_phase(pl.n_phases - 1);  // every wave passes every barrier
     st.lds_slots = lds_next * ipt;
@@ -767,6 +786,8 @@ std::vector<std::string> emit_chunks(const Graph& g, const Plan& plan, const Emi
     tot.spills += ces.back()->st.spills;
     tot.lds_slots = std::max(tot.lds_slots, ces.back()->st.lds_slots);
     tot.extra_ws = std::max(tot.extra_ws, ces.back()->st.extra_ws);
+    tot.ws_ops += ces.back()->st.ws_ops;
+    tot.lds_ops += ces.back()->st.lds_ops;
   }
   const int64_t ns = (int64_t)extra_ws_base + tot.extra_ws;  // workspace slots per instance
   std::vector<std::string> srcs;
@@ -777,6 +798,7 @@ std::vector<std::string> emit_chunks(const Graph& g, const Plan& plan, const Emi
     s += "// generated by xg: chunk " + std::to_string(c) + " of " + std::to_string(nc) + "\n";
     s += contract_pragma(eo.strict);
     s += emit_preamble(g, eo);
+    s += contract_end(eo.strict, g);
     s += "extern \"C\" __global__ void __launch_bounds__(" + std::to_string(eo.block) + ") " +
          prefix + "_c" + std::to_string(c) + "(long long n";
     for (size_t a = 0; a < g.nnz_in.size(); ++a)
@@ -813,14 +835,20 @@ std::string buffer_helpers(bool f32) {
   return s;
 }
 
-// Outside strict mode the generated code lets the compiler fuse a multiply
-// and a dependent add across statements into one FMA.  The permission is
-// given by this pragma (per instruction) with -ffp-contract=on, not by
-// -ffp-contract=fast: the latter is a code-generator setting that also fuses
-// inside linked device-library functions, whose error-free transformations
-// rely on separate roundings (pow lost up to 26 ulp that way).
+// Outside strict mode the inline math helpers let the compiler fuse a
+// multiply and a dependent add across statements into one FMA.  The
+// permission is given by this pragma (per instruction) with
+// -ffp-contract=on, not by -ffp-contract=fast: the latter is a
+// code-generator setting that also fuses inside linked device-library
+// functions, whose error-free transformations rely on separate roundings
+// (pow lost up to 26 ulp that way).  The programs' own statements come after
+// contract_end: their fused multiply-adds are written out
+// (fuse_multiply_adds), so that every plan of a program rounds alike.
 std::string contract_pragma(bool strict) {
   return strict ? std::string() : std::string("#pragma clang fp contract(fast)\n");
+}
+std::string contract_end(bool strict, const Graph& g) {
+  return strict || mixed_precision(g) ? std::string() : std::string("#pragma clang fp contract(off)\n");
 }
 
 std::string emit_preamble(const Graph& g, const EmitOptions& eo) {
@@ -916,6 +944,7 @@ std::vector<std::string> emit_wide(const Graph& g, const Plan& plan, const EmitO
        std::to_string(plan.n_phases) + " phases, " + std::to_string(plan.chunks.size()) + " chunks\n";
   s += contract_pragma(eo.strict);
   s += emit_preamble(g, eo);
+  s += contract_end(eo.strict, g);
   s += args;
   // kernel arguments are 8-byte values laid out back to back, as in XgArgs;
   // the implicit arguments follow them (checked on the host against the
@@ -978,6 +1007,8 @@ PhasedBranches phased_branches(const Graph& g, const Plan& plan, const EmitOptio
     ce.run();
     pb.st.spills += ce.st.spills;
     pb.st.lds_slots = std::max(pb.st.lds_slots, ce.st.lds_slots);
+    pb.st.ws_ops += ce.st.ws_ops;
+    pb.st.lds_ops += ce.st.lds_ops;
     pb.code += std::string(c == 0 ? "  if" : "  else if") + " (xg_w == " + std::to_string(c) + ") {\n";
     pb.code += ce.out;
     pb.code += "  }\n";
@@ -997,6 +1028,7 @@ std::vector<std::string> emit_phased(const Graph& g, const Plan& plan, const Emi
        std::to_string(plan.n_phases) + " phases, " + std::to_string(plan.n_xch) + " exchange slots\n";
   s += contract_pragma(eo.strict);
   s += emit_preamble(g, eo);
+  s += contract_end(eo.strict, g);
   s += "#define xg_barrier() __syncthreads()\n";
   s += "extern \"C\" __global__ void __launch_bounds__(" + std::to_string(64 * W) + ") " + prefix +
        "_c0(long long n";

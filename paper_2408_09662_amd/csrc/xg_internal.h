@@ -17,8 +17,15 @@ struct Node {
   uint8_t op;
   uint8_t f32 = 0;  // computed in binary32 inside an f64 program
   int32_t a = -1, b = -1;
+  int32_t c = -1;   // third operand (fused multiply-adds only)
   int64_t aux = 0;
 };
+
+// Fused multiply-adds, made by fuse_multiply_adds (never in a program's
+// instruction list): a*b + c, a*b - c, c - a*b, each rounded once.
+constexpr int kOpFma = XG_OP_COUNT, kOpFms = XG_OP_COUNT + 1, kOpFnma = XG_OP_COUNT + 2;
+constexpr int kOpEnd = XG_OP_COUNT + 3;
+inline bool is_fma(int op) { return op >= kOpFma && op < kOpEnd; }
 
 struct Graph {
   int dtype = XG_F64;
@@ -44,6 +51,20 @@ void cse(Graph& g);
 // more rounding); callers skip it in strict mode.  Returns the number of
 // divisions replaced.
 int64_t share_reciprocals(Graph& g);
+
+// Negations move out of products and quotients and into the sums that read
+// them (x + -y is x - y); every result keeps its bits, signs of zeros
+// included.  With `merge`, equal operations that appear so become one (not
+// for an adjoint, whose recomputed ranges repeat operations on purpose).
+// Callers skip it in strict mode.
+void fold_negations(Graph& g, bool merge);
+
+// Sums and differences with a product become fused multiply-adds where that
+// removes the product (each of its uses is such a sum).  Which product joins
+// which sum is decided here, on the whole graph, so every plan of a program
+// (one wave or several, chunks, a batch) rounds alike.  Callers skip it in
+// strict mode.  Returns the number of fused sums.
+int64_t fuse_multiply_adds(Graph& g);
 
 // Reverse-mode adjoint as a program transformation.  The result's inputs
 // are g's inputs followed by one seed argument per output of g (same
@@ -91,6 +112,7 @@ struct Plan {
   // from their exchange slots right after the barrier that starts phase k
   std::vector<std::vector<int32_t>> mailbox;
   int64_t coop_est = 0;  // modelled time of the phased plan (cost units)
+  int32_t phase_len = 0; // phased plan: the phase length it was made with
 };
 
 struct PlanOptions {
@@ -98,7 +120,11 @@ struct PlanOptions {
   int waves = 1;
   int coop_phase = 0;  // > 0 with waves > 1: phased plan, this much work per wave and phase
   int64_t xch_cap = 0; // most LDS exchange slots the phased plan may use
+  int64_t lds_slots = 0; // LDS slots of 64 lanes in all (exchanges and spills)
+  int reg_budget = 0;  // values a wave holds in registers
 };
+// coop_phase of a phased plan that chooses its phases' length itself
+constexpr int kAutoPhase = -1;
 
 // Relative issue cost of one operation (wave instructions, roughly).
 int op_cost(int op);
@@ -127,6 +153,8 @@ struct EmitStats {
   int32_t lds_slots = 0;
   int32_t spills = 0;
   int32_t extra_ws = 0;  // global spill slots beyond LDS capacity
+  int64_t ws_ops = 0;    // workspace loads and stores of one instance
+  int64_t lds_ops = 0;   // LDS loads and stores of one instance
 };
 
 // Phased cooperative-tile program (plan.phased): one source, one kernel
@@ -209,9 +237,15 @@ bool compile_hip(const std::string& src, const std::vector<std::string>& opts, C
 bool compile_many(const std::vector<std::string>& srcs, const std::vector<std::string>& opts,
                   std::vector<CodeObject>& cos, std::string& err, bool verbose);
 std::vector<std::string> base_compile_options(bool strict);
-// First line of a generated source: the FMA-contraction permission (none in
-// strict mode).
+// First line of a generated source: the FMA-contraction permission for its
+// math helpers (none in strict mode); contract_end takes it back for the
+// program's own statements.
 std::string contract_pragma(bool strict);
+std::string contract_end(bool strict, const Graph& g);
+// Whether g is a binary64 program with binary32-tagged operations.  The
+// compiler contracts its statements (a binary32 rounding that moves to another
+// operation shows in its binary64 results), in the plan it always had.
+bool mixed_precision(const Graph& g);
 // Resources of `kernel` from its kernel descriptor in the code object.
 struct KernelDesc {
   uint32_t lds_bytes = 0;      // group segment (static LDS) per workgroup

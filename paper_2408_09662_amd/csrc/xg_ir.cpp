@@ -154,6 +154,7 @@ void dce(Graph& g) {
     const Node& nd = g.nodes[i];
     if (nd.a >= 0) live[nd.a] = 1;
     if (nd.b >= 0) live[nd.b] = 1;
+    if (nd.c >= 0) live[nd.c] = 1;
   }
   std::vector<int32_t> remap(n, -1);
   std::vector<Node> nodes;
@@ -163,6 +164,7 @@ void dce(Graph& g) {
     Node nd = g.nodes[i];
     if (nd.a >= 0) nd.a = remap[nd.a];
     if (nd.b >= 0) nd.b = remap[nd.b];
+    if (nd.c >= 0) nd.c = remap[nd.c];
     remap[i] = (int32_t)nodes.size();
     nodes.push_back(nd);
   }
@@ -252,6 +254,159 @@ int64_t share_reciprocals(Graph& g) {
   g.nodes.swap(nodes);
   for (auto& arg : g.out) for (int32_t& v : arg) v = remap[v];
   return replaced;
+}
+
+bool mixed_precision(const Graph& g) {
+  for (const Node& nd : g.nodes)
+    if (nd.f32) return true;
+  return false;
+}
+
+void fold_negations(Graph& g, bool merge) {
+  const int32_t n = (int32_t)g.nodes.size();
+  std::vector<Node> nodes;
+  nodes.reserve(n);
+  std::unordered_map<Key, int32_t, KeyHash> memo;
+  auto node = [&](uint8_t op, int32_t a, int32_t b, int64_t aux, uint8_t f32) -> int32_t {
+    if ((op == XG_OP_ADD || op == XG_OP_MUL) && a > b) std::swap(a, b);
+    Key k{op, f32, a, b, aux};
+    if (merge || op == XG_OP_INPUT || op == XG_OP_CONST) {
+      auto it = memo.find(k);
+      if (it != memo.end()) return it->second;
+    }
+    Node q;
+    q.op = op; q.f32 = f32; q.a = a; q.b = b; q.aux = aux;
+    nodes.push_back(q);
+    memo.emplace(k, (int32_t)nodes.size() - 1);
+    return (int32_t)nodes.size() - 1;
+  };
+  // old value v is new value rep[v], negated if neg[v]
+  std::vector<int32_t> rep(n, -1);
+  std::vector<char> neg(n, 0);
+  auto value = [&](int32_t v) { return neg[v] ? node(XG_OP_NEG, rep[v], -1, 0, nodes[rep[v]].f32) : rep[v]; };
+  // -x - y, as (-x) - y or (-y) - x: the negated one is not a product, so
+  // that a product can still join the sum
+  auto minus_both = [&](int32_t x, int32_t y, uint8_t f) {
+    const Node& q = nodes[x];
+    if (q.op == XG_OP_MUL || q.op == XG_OP_SQ || (q.op == XG_OP_ADD && q.a == q.b)) std::swap(x, y);
+    const int32_t m = node(XG_OP_NEG, x, -1, 0, nodes[x].f32);
+    return node(XG_OP_SUB, m, y, 0, f);
+  };
+  for (int32_t i = 0; i < n; ++i) {
+    const Node& nd = g.nodes[i];
+    const int32_t a = nd.a, b = nd.b;
+    const uint8_t f = nd.f32;
+    const bool na = a >= 0 && neg[a], nb = b >= 0 && neg[b];
+    switch (nd.op) {
+      case XG_OP_NEG:
+        if (nodes[rep[a]].f32 != f) {  // it also rounds: kept
+          rep[i] = node(XG_OP_NEG, value(a), -1, 0, f);
+        } else {
+          rep[i] = rep[a];
+          neg[i] = !na;
+        }
+        break;
+      case XG_OP_MUL: case XG_OP_DIV:
+        rep[i] = node(nd.op, rep[a], rep[b], 0, f);
+        neg[i] = na != nb;
+        break;
+      case XG_OP_SQ: case XG_OP_FABS:
+        rep[i] = node(nd.op, rep[a], -1, 0, f);
+        break;
+      case XG_OP_ADD:  // (-a) + (-b) keeps one negation: -(a + b) has another sign of zero
+        if (na && nb && rep[a] == rep[b]) {  // (the doubling -(x + x) keeps it)
+          rep[i] = node(XG_OP_ADD, rep[a], rep[a], 0, f);
+          neg[i] = 1;
+        } else if (na && nb) rep[i] = minus_both(rep[a], rep[b], f);
+        else if (nb) rep[i] = node(XG_OP_SUB, rep[a], rep[b], 0, f);
+        else if (na) rep[i] = node(XG_OP_SUB, rep[b], rep[a], 0, f);
+        else rep[i] = node(XG_OP_ADD, rep[a], rep[b], 0, f);
+        break;
+      case XG_OP_SUB:
+        if (na && nb) rep[i] = node(XG_OP_SUB, rep[b], rep[a], 0, f);
+        else if (nb) rep[i] = node(XG_OP_ADD, rep[a], rep[b], 0, f);
+        else if (na) rep[i] = minus_both(rep[a], rep[b], f);
+        else rep[i] = node(XG_OP_SUB, rep[a], rep[b], 0, f);
+        break;
+      default:
+        rep[i] = node(nd.op, a >= 0 ? value(a) : -1, b >= 0 ? value(b) : -1, nd.aux, f);
+    }
+  }
+  for (auto& arg : g.out) for (int32_t& v : arg) v = value(v);
+  g.nodes.swap(nodes);
+  dce(g);
+}
+
+int64_t fuse_multiply_adds(Graph& g) {
+  const int32_t n = (int32_t)g.nodes.size();
+  // products, and doublings x + x (exact, so 2 x + y rounds as before)
+  auto product = [&](int32_t v) {
+    if (v < 0) return false;
+    const Node& nd = g.nodes[v];
+    return nd.op == XG_OP_MUL || nd.op == XG_OP_SQ || (nd.op == XG_OP_ADD && nd.a == nd.b);
+  };
+  // users of each product; a product that is an output, or that anything
+  // but a sum of its own precision reads, stays
+  std::vector<std::vector<int32_t>> users(n);
+  std::vector<char> stays(n, 0);
+  for (auto& arg : g.out) for (int32_t v : arg) stays[v] = 1;
+  for (int32_t v = 0; v < n; ++v) {
+    const Node& nd = g.nodes[v];
+    const bool sum = (nd.op == XG_OP_ADD || nd.op == XG_OP_SUB) && nd.a != nd.b;
+    for (int32_t o : {nd.a, nd.b}) {
+      if (!product(o)) continue;
+      if (sum && g.nodes[o].f32 == nd.f32) users[o].push_back(v);
+      else stays[o] = 1;
+    }
+  }
+  // each sum takes one product; removing a product saves one operation
+  // whatever its number of users, so products with few users come first
+  // (each more user could have taken another product)
+  size_t most = 0;
+  for (int32_t v = 0; v < n; ++v)
+    if (!stays[v]) most = std::max(most, users[v].size());
+  std::vector<int32_t> takes(n, -1);
+  int64_t fused = 0;
+  for (size_t k = 1; k <= most; ++k)
+    for (int32_t v = 0; v < n; ++v) {
+      if (!product(v) || stays[v] || users[v].size() != k) continue;
+      bool free = true;
+      for (int32_t u : users[v]) free = free && takes[u] < 0;
+      if (!free) continue;
+      for (int32_t u : users[v]) { takes[u] = v; ++fused; }
+    }
+  if (fused == 0) return 0;
+  // the constant 2.0, first in the list (operands precede their users)
+  int32_t two_c = -1;
+  for (size_t i = 0; i < g.consts.size(); ++i)
+    if (g.consts[i] == 2.0) { two_c = (int32_t)i; break; }
+  if (two_c < 0) { two_c = (int32_t)g.consts.size(); g.consts.push_back(2.0); }
+  std::vector<Node> nodes;
+  nodes.reserve(n + 1);
+  Node two;
+  two.op = XG_OP_CONST;
+  two.aux = two_c;
+  nodes.push_back(two);
+  for (int32_t v = 0; v < n; ++v) {
+    Node nd = g.nodes[v];
+    if (takes[v] >= 0) {
+      const Node& m = g.nodes[takes[v]];
+      const bool first = nd.a == takes[v];
+      nd.c = first ? nd.b : nd.a;
+      nd.op = (uint8_t)(nd.op == XG_OP_ADD ? kOpFma : first ? kOpFms : kOpFnma);
+      nd.a = m.a;
+      nd.b = m.op == XG_OP_MUL ? m.b : m.op == XG_OP_SQ ? m.a : -2;  // -2: the constant 2.0
+    }
+    if (nd.a >= 0) ++nd.a;
+    if (nd.b >= 0) ++nd.b;
+    if (nd.b == -2) nd.b = 0;
+    if (nd.c >= 0) ++nd.c;
+    nodes.push_back(nd);
+  }
+  g.nodes.swap(nodes);
+  for (auto& arg : g.out) for (int32_t& v : arg) ++v;
+  dce(g);
+  return fused;
 }
 
 }  // namespace xg

@@ -46,7 +46,11 @@ std::vector<std::string> base_compile_options(bool strict) {
           strict ? "-ffp-contract=off" : "-ffp-contract=on",
           "-fno-gpu-flush-denormals-to-zero",
           // packed fp32 arithmetic is switched off for all generated code
-          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"};
+          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          // this pass prepares branches and addresses, which the sources
+          // have none of, and takes time quadratic in a block's length (half
+          // of the 72 s that a 36,000-statement kernel took)
+          "-mllvm", "-disable-cgp"};
 }
 
 std::string cache_dir() {

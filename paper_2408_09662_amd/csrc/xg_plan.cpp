@@ -10,8 +10,11 @@
 // are cut into chunks (one kernel each) at positions where few values are
 // live; values that cross a cut go to a structure-of-arrays workspace.
 #include <algorithm>
+#include <atomic>
 #include <queue>
 #include <stdexcept>
+#include <system_error>
+#include <thread>
 
 #include "xg_internal.h"
 
@@ -20,11 +23,12 @@ namespace xg {
 namespace {
 
 // Distinct non-constant operands of node i.
-inline int operands(const Graph& g, int32_t i, int32_t ops[2]) {
+inline int operands(const Graph& g, int32_t i, int32_t ops[3]) {
   const Node& nd = g.nodes[i];
   int k = 0;
   if (nd.a >= 0 && g.nodes[nd.a].op != XG_OP_CONST) ops[k++] = nd.a;
   if (nd.b >= 0 && nd.b != nd.a && g.nodes[nd.b].op != XG_OP_CONST) ops[k++] = nd.b;
+  if (nd.c >= 0 && nd.c != nd.a && nd.c != nd.b && g.nodes[nd.c].op != XG_OP_CONST) ops[k++] = nd.c;
   return k;
 }
 
@@ -42,22 +46,22 @@ std::vector<int32_t> greedy_order(const Graph& g) {
   std::vector<int32_t> pending(n, 0), remaining(n, 0);
   for (int32_t i = 0; i < n; ++i) {
     if (g.nodes[i].op == XG_OP_CONST) continue;
-    int32_t ops[2];
+    int32_t ops[3];
     int k = operands(g, i, ops);
     pending[i] = k;
     for (int j = 0; j < k; ++j) { cons[ops[j]].push_back(i); remaining[ops[j]]++; }
   }
   std::vector<char> done(n, 0);
   auto score = [&](int32_t i) {
-    int32_t ops[2];
+    int32_t ops[3];
     int k = operands(g, i, ops);
     int s = 0;
     for (int j = 0; j < k; ++j) if (remaining[ops[j]] == 1) ++s;
     if (!cons[i].empty()) s -= 1;
-    return s + 1;  // 0..3
+    return s + 1;  // 0..4
   };
   typedef std::priority_queue<int32_t, std::vector<int32_t>, std::greater<int32_t>> MinQ;
-  MinQ q[4];
+  MinQ q[5];
   std::vector<int8_t> cur(n, -1);
   auto push = [&](int32_t i) {
     int s = score(i);
@@ -70,7 +74,7 @@ std::vector<int32_t> greedy_order(const Graph& g) {
   order.reserve(n);
   while (true) {
     int32_t pick = -1;
-    for (int s = 3; s >= 0 && pick < 0; --s) {
+    for (int s = 4; s >= 0 && pick < 0; --s) {
       while (!q[s].empty()) {
         int32_t i = q[s].top();
         q[s].pop();
@@ -82,7 +86,7 @@ std::vector<int32_t> greedy_order(const Graph& g) {
     if (pick < 0) break;
     done[pick] = 1;
     order.push_back(pick);
-    int32_t ops[2];
+    int32_t ops[3];
     int k = operands(g, pick, ops);
     for (int j = 0; j < k; ++j) {
       int32_t v = ops[j];
@@ -110,7 +114,7 @@ int64_t max_live_of(const Graph& g, const std::vector<int32_t>& order) {
   const int32_t n = (int32_t)g.nodes.size();
   std::vector<int32_t> last(n, -1);
   for (int32_t p = 0; p < (int32_t)order.size(); ++p) {
-    int32_t ops[2];
+    int32_t ops[3];
     int k = operands(g, order[p], ops);
     for (int j = 0; j < k; ++j) last[ops[j]] = p;
   }
@@ -131,7 +135,8 @@ int op_cost(int op) {
     case XG_OP_SQRT: return 8;
     case XG_OP_SIN: case XG_OP_COS: case XG_OP_TAN: case XG_OP_EXP: case XG_OP_LOG:
     case XG_OP_TANH: case XG_OP_ATAN: case XG_OP_POW: case XG_OP_ATAN2: return 40;
-    case XG_OP_INPUT: case XG_OP_OUTPUT: case XG_OP_CONST: case XG_OP_ASSIGN: return 0;
+    case XG_OP_INPUT: case XG_OP_OUTPUT: case XG_OP_CONST: case XG_OP_ASSIGN:
+    case XG_OP_NEG: return 0;  // (a negation is a source modifier of what reads it)
   }
   return 1;
 }
@@ -151,7 +156,7 @@ static Plan make_wide_plan(const Graph& g, const PlanOptions& po) {
   for (int32_t v = 0; v < n; ++v) {
     const Node& nd = g.nodes[v];
     if (nd.op == XG_OP_CONST || nd.op == XG_OP_INPUT) continue;
-    int32_t ops[2];
+    int32_t ops[3];
     int k = operands(g, v, ops);
     int32_t l = 0;
     for (int j = 0; j < k; ++j) l = std::max(l, lvl[ops[j]]);
@@ -215,7 +220,7 @@ static Plan make_wide_plan(const Graph& g, const PlanOptions& po) {
   std::vector<char> crosses(n, 0);
   for (size_t c = 0; c < pl.chunks.size(); ++c)
     for (int32_t p = pl.chunks[c].begin; p < pl.chunks[c].end; ++p) {
-      int32_t ops[2];
+      int32_t ops[3];
       int k = operands(g, pl.order[p], ops);
       for (int j = 0; j < k; ++j) {
         const int32_t u = ops[j];
@@ -257,7 +262,7 @@ static Plan make_wide_plan(const Graph& g, const PlanOptions& po) {
   // workspace written in an earlier phase; a slot's occupants never overlap
   for (size_t c = 0; c < pl.chunks.size(); ++c)
     for (int32_t p = pl.chunks[c].begin; p < pl.chunks[c].end; ++p) {
-      int32_t ops[2];
+      int32_t ops[3];
       int k = operands(g, pl.order[p], ops);
       for (int j = 0; j < k; ++j) {
         const int32_t u = ops[j];
@@ -286,13 +291,30 @@ static Plan make_wide_plan(const Graph& g, const PlanOptions& po) {
 // phase by phase: in each phase every wave takes ready clusters until it
 // holds `coop_phase` cost units, a cluster being ready on a wave when each
 // value it needs (through its duplicated operands too) was computed in an
-// earlier phase or earlier on that wave.  A wave prefers clusters whose
-// operands it computed itself (fewer exchanged values), then the longest
-// remaining path.  A value read by a wave other than its own goes through
+// earlier phase or earlier on that wave.  A wave takes the ready cluster that
+// comes first (by its remaining path, or by its place in the low-pressure
+// order, which keeps live sets short), less what it would add here: loads of
+// values the wave does not hold, stores of values nobody exported, duplicated
+// operands.  A value read by a wave other than its own goes through
 // an LDS exchange slot: written when computed, copied by each reading wave
 // right after the barrier that ends its phase (a slot lives for one
 // barrier); values stay in their wave's registers otherwise.
 namespace {
+
+// What exchanges cost a wave, in units of one vector operation (measured
+// with four waves at work, each on its own SIMD, on 512-byte operands: a load
+// from LDS takes the issuing wave 12.7 cycles beside a vector operation's 4,
+// a store 20.7, a workgroup barrier 140).
+constexpr int64_t kLoadCost = 3, kStoreCost = 5, kBarrierCost = 35;
+// An eviction and its reload, issued well before the use (twice that through
+// the workspace): the MPC on 2 waves, 45,000 units without its 2,800 spills,
+// measured 58,000.
+constexpr int64_t kSpillCost = 4;
+
+struct Policy {
+  bool by_order;   // rank by place in the low-pressure order (else longest path)
+  int64_t weight;  // of what a choice adds in loads, stores and duplication
+};
 
 struct PhasedResult {
   std::vector<std::vector<int32_t>> lists;    // per wave: node ids in order
@@ -303,7 +325,7 @@ struct PhasedResult {
   int64_t est = 0;                            // modelled time (cost units)
 };
 
-PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, int64_t cut_max) {
+PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, int64_t cut_max, Policy policy) {
   const int32_t n = (int32_t)g.nodes.size();
   auto sched = [&](int32_t v) {
     const int op = g.nodes[v].op;
@@ -314,7 +336,7 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
   for (auto& a : g.out) for (int32_t v : a) is_out[v] = 1;
   for (int32_t v = 0; v < n; ++v) {
     if (!sched(v)) continue;
-    int32_t ops[2];
+    int32_t ops[3];
     int k = operands(g, v, ops);
     for (int j = 0; j < k; ++j) { nuse[ops[j]]++; single[ops[j]] = v; }
   }
@@ -326,7 +348,7 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
   std::vector<char> cut(n, 0);
   for (int32_t v = 0; v < n; ++v) {
     if (!sched(v)) continue;
-    int32_t ops[2];
+    int32_t ops[3];
     int k = operands(g, v, ops);
     int64_t t = op_cost(g.nodes[v].op);
     for (int j = 0; j < k; ++j)
@@ -351,7 +373,7 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
     for (int32_t v : members[r]) {
       ccost[r] += op_cost(g.nodes[v].op);
       has_out = has_out || is_out[v];
-      int32_t ops[2];
+      int32_t ops[3];
       int k = operands(g, v, ops);
       for (int j = 0; j < k; ++j) {
         const int32_t u = ops[j];
@@ -397,23 +419,30 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
     for (int32_t s : esucc[*it]) m = std::max(m, bl[s]);
     bl[*it] = ccost[*it] + m;
   }
-  struct Key {
-    int32_t local;
-    int64_t bl;
-    int32_t r;
-    bool operator<(const Key& o) const {  // max-heap: more local, longer path, smaller id
-      if (local != o.local) return local < o.local;
-      if (bl != o.bl) return bl < o.bl;
-      return r > o.r;
-    }
-  };
-  std::vector<std::priority_queue<Key>> ready(W);
-  std::vector<std::vector<int32_t>> miss(W, std::vector<int32_t>(n, 0)), nloc(W, std::vector<int32_t>(n, 0));
+  // Ready clusters of a wave, and which exchanged values it holds (computed
+  // or received).  A wave takes the ready cluster with the largest score:
+  // the rank its policy gives (the longest remaining path, or the place in
+  // the low-pressure order), less what taking it here would add in loads of
+  // values the wave does not hold, stores of values nobody exported yet and
+  // duplicated operands.
+  std::vector<int64_t> rank(n, 0);
+  if (policy.by_order) {
+    std::vector<int64_t> at(n, 0);
+    int64_t t = 0;
+    for (int32_t v : low_pressure_order(g)) { t += op_cost(g.nodes[v].op); at[v] = t; }
+    for (int32_t r : sc) rank[r] = -at[r] / W;
+  } else {
+    for (int32_t r : sc) rank[r] = bl[r];
+  }
+  std::vector<std::vector<int32_t>> ready(W);
+  std::vector<std::vector<int32_t>> miss(W, std::vector<int32_t>(n, 0));
   std::vector<std::vector<char>> have(W, std::vector<char>(n, 0));  // duplicated clusters on each wave
+  std::vector<std::vector<char>> held(W, std::vector<char>(n, 0));  // exchanged values on each wave
+  std::vector<char> exported(n, 0);
   for (int w = 0; w < W; ++w)
     for (int32_t r : sc) {
       miss[w][r] = (int32_t)eff[r].size();
-      if (miss[w][r] == 0) ready[w].push({0, bl[r], r});
+      if (miss[w][r] == 0) ready[w].push_back(r);
     }
   PhasedResult res;
   res.lists.assign(W, {});
@@ -421,7 +450,6 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
   res.node_phase.assign(n, -1);
   res.owner.assign(n, -1);
   std::vector<char> done(n, 0);
-  std::vector<int32_t> cphase(n, -1), cwave(n, -1);
   size_t remaining = sc.size();
   int32_t phase = 0;
   std::vector<std::vector<int64_t>> loads;
@@ -435,8 +463,6 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
       int w = -1;
       for (int x = 0; x < W; ++x)
         if (active[x] && (w < 0 || load[x] < load[w])) w = x;
-      auto& q = ready[w];
-      while (!q.empty() && done[q.top().r]) q.pop();
       // a phase lasts at least T; once a wave took a large cluster, the
       // others fill up to its load (they would wait at the barrier anyway).
       // While some wave has nothing to do, the phase is cut short instead:
@@ -444,208 +470,276 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
       int64_t target = T;
       for (int x = 0; x < W; ++x) target = std::max(target, load[x]);
       if (starved) target = std::max<int64_t>(40, T / 4);
-      if (q.empty() || load[w] >= target) {
-        if (q.empty()) starved = true;
+      int32_t r = -1;
+      int64_t best = 0, comm = 0;
+      size_t keep = 0;
+      auto& q = ready[w];
+      for (size_t i = 0; i < q.size(); ++i) {
+        const int32_t c = q[i];
+        if (done[c]) continue;
+        q[keep++] = c;
+        int64_t x = 0;
+        for (int32_t p : eff[c])
+          if (!held[w][p]) x += kLoadCost + (exported[p] ? 0 : kStoreCost);
+        int64_t y = 0;
+        for (int32_t d : cone[c])
+          if (!have[w][d]) y += ccost[d];
+        const int64_t sco = rank[c] - policy.weight * (x + y);
+        if (r < 0 || sco > best || (sco == best && c < r)) { r = c; best = sco; comm = x; }
+      }
+      q.resize(keep);
+      if (r < 0 || load[w] >= target) {
+        if (r < 0) starved = true;
         active[w] = 0;
         --n_active;
         continue;
       }
-      const int32_t r = q.top().r;
-      q.pop();
       done[r] = 1;
       --remaining;
+      for (int32_t p : eff[r])
+        if (!held[w][p]) { held[w][p] = 1; exported[p] = 1; }
       for (int32_t d : cone[r]) {
         if (have[w][d]) continue;
         have[w][d] = 1;
         load[w] += ccost[d];
         for (int32_t v : members[d]) { res.lists[w].push_back(v); res.phases[w].push_back(phase); }
       }
-      load[w] += ccost[r];
+      load[w] += ccost[r] + comm;
       for (int32_t v : members[r]) {
         res.lists[w].push_back(v);
         res.phases[w].push_back(phase);
         res.node_phase[v] = phase;
         res.owner[v] = w;
       }
-      cphase[r] = phase;
-      cwave[r] = w;
+      held[w][r] = 1;
       newly.push_back({w, r});
-      for (int32_t s : esucc[r]) {
-        nloc[w][s]++;
-        if (--miss[w][s] == 0 && !done[s]) ready[w].push({nloc[w][s], bl[s], s});
-      }
+      for (int32_t s : esucc[r])
+        if (--miss[w][s] == 0 && !done[s]) ready[w].push_back(s);
     }
     if (newly.empty()) throw std::logic_error("phased plan: no cluster became ready");
     for (auto& wr : newly)
       for (int x = 0; x < W; ++x) {
         if (x == wr.first) continue;
         for (int32_t s : esucc[wr.second])
-          if (--miss[x][s] == 0 && !done[s]) ready[x].push({nloc[x][s], bl[s], s});
+          if (--miss[x][s] == 0 && !done[s]) ready[x].push_back(s);
       }
     loads.push_back(load);
     ++phase;
   }
   res.n_phases = phase;
-  // modelled time: per phase the slowest wave, each exchanged value costing
-  // its producer a store and each reading wave a load, plus a barrier
-  std::vector<std::vector<int64_t>> xfer(phase + 1, std::vector<int64_t>(W, 0));
-  for (int w = 0; w < W; ++w) {
-    std::vector<char> got(n, 0);
-    for (int32_t v : res.lists[w]) {
-      int32_t ops[2];
-      int k = operands(g, v, ops);
-      for (int j = 0; j < k; ++j) {
-        const int32_t u = ops[j];
-        if (g.nodes[u].op == XG_OP_INPUT || res.owner[u] < 0 || res.owner[u] == w || got[u]) continue;
-        got[u] = 1;
-        xfer[res.node_phase[u] + 1][w] += 1;
-        xfer[res.node_phase[u]][res.owner[u]] += 1;
-      }
-    }
-  }
+  // modelled time: per phase the slowest wave (its loads of other waves'
+  // values are in its load already; its stores are added here) and a barrier
+  std::vector<std::vector<int64_t>> stores(phase + 1, std::vector<int64_t>(W, 0));
+  for (int32_t r : sc)
+    if (exported[r]) stores[res.node_phase[r]][res.owner[r]] += 1;
   res.est = 0;
   for (int32_t k = 0; k < phase; ++k) {
     int64_t m = 0;
-    for (int w = 0; w < W; ++w) m = std::max(m, loads[k][w] + xfer[k][w]);
-    res.est += m + 30;
+    for (int w = 0; w < W; ++w) m = std::max(m, loads[k][w] + kStoreCost * stores[k][w]);
+    res.est += m + kBarrierCost;
   }
   return res;
 }
 
 }  // namespace
 
-static Plan make_phased_plan(const Graph& g, const PlanOptions& po) {
+// The phased plan of one setting: phases of at least T, duplication threshold
+// D, subtree cap S.
+static Plan phased_plan_of(const Graph& g, const PlanOptions& po, int64_t T, int64_t D, int64_t S, Policy policy) {
   const int32_t n = (int32_t)g.nodes.size();
   const int W = po.waves;
-  const int64_t T = std::max(1, po.coop_phase);
-  // duplicate clusters of up to 1, 2, 4 or 8 cost units: the plan with the
-  // best modelled time among those whose exchange fits the LDS allowance
-  Plan best;
-  int64_t best_est = INT64_MAX;
-  bool best_lds_only = false;
-  std::string why = "phased plan: no duplication threshold fits the LDS";
-  for (int64_t D : {1, 2, 4, 8})
-  for (int64_t S : {0, 32, 96}) {
-    PhasedResult r = phased_schedule(g, W, T, D, S);
-    Plan pl;
-    pl.waves = W;
-    pl.phased = true;
-    pl.n_phases = r.n_phases;
-    pl.node_phase = r.node_phase;
-    // schedule: wave 0's nodes, then wave 1's, ...; one chunk per wave
-    for (int w = 0; w < W; ++w) {
-      const int32_t begin = (int32_t)pl.order.size();
-      if (w == 0)  // inputs that are outputs themselves are stored by wave 0
-        for (int32_t v = 0; v < n; ++v)
-          if (g.nodes[v].op == XG_OP_INPUT) { pl.order.push_back(v); pl.pos_phase.push_back(0); }
-      for (size_t i = 0; i < r.lists[w].size(); ++i) {
-        pl.order.push_back(r.lists[w][i]);
-        pl.pos_phase.push_back(r.phases[w][i]);
-      }
-      pl.chunks.push_back({begin, (int32_t)pl.order.size()});
-      pl.chunk_wave.push_back(w);
-      pl.chunk_phase.push_back(0);
+  PhasedResult r = phased_schedule(g, W, T, D, S, policy);
+  Plan pl;
+  pl.waves = W;
+  pl.phased = true;
+  pl.n_phases = r.n_phases;
+  pl.node_phase = r.node_phase;
+  // schedule: wave 0's nodes, then wave 1's, ...; one chunk per wave
+  for (int w = 0; w < W; ++w) {
+    const int32_t begin = (int32_t)pl.order.size();
+    if (w == 0)  // inputs that are outputs themselves are stored by wave 0
+      for (int32_t v = 0; v < n; ++v)
+        if (g.nodes[v].op == XG_OP_INPUT) { pl.order.push_back(v); pl.pos_phase.push_back(0); }
+    for (size_t i = 0; i < r.lists[w].size(); ++i) {
+      pl.order.push_back(r.lists[w][i]);
+      pl.pos_phase.push_back(r.phases[w][i]);
     }
-    for (int32_t v = 0; v < n; ++v)
-      if (is_arith(g.nodes[v].op)) pl.n_ops++;
-    for (auto& ch : pl.chunks) {
-      std::vector<int32_t> part(pl.order.begin() + ch.begin, pl.order.begin() + ch.end);
-      pl.max_live = std::max(pl.max_live, max_live_of(g, part));
-    }
-    // exchange slots (values other waves read) and each wave's mailbox
-    pl.ws_slot.assign(n, -1);
-    pl.xch_slot.assign(n, -1);
-    pl.mailbox.assign((size_t)W * (pl.n_phases + 1), {});
-    std::vector<char> remote(n, 0);
+    pl.chunks.push_back({begin, (int32_t)pl.order.size()});
+    pl.chunk_wave.push_back(w);
+    pl.chunk_phase.push_back(0);
+  }
+  for (int32_t v = 0; v < n; ++v)
+    if (is_arith(g.nodes[v].op)) pl.n_ops++;
+  // values each wave holds (another wave's from the phase after its own on),
+  // and how many leave its registers: every rise of the held count beyond
+  // the budget is an eviction and, later, a reload
+  int64_t spilled = 0, most_over = 0;
+  {
+    std::vector<int64_t> evicted(W, 0);
     for (int w = 0; w < W; ++w) {
-      std::vector<char> got(n, 0);
       const Chunk& ch = pl.chunks[w];
-      for (int32_t p = ch.begin; p < ch.end; ++p) {
-        const int32_t v = pl.order[p];
-        if (g.nodes[v].op == XG_OP_INPUT) continue;
-        int32_t ops[2];
+      const int32_t len = ch.end - ch.begin;
+      std::vector<int32_t> last(n, -1), start(n, -1);
+      std::vector<int32_t> phase_at(pl.n_phases + 1, len);
+      for (int32_t p = len - 1; p >= 0; --p) phase_at[pl.pos_phase[ch.begin + p]] = p;
+      for (int32_t k = pl.n_phases - 1; k >= 0; --k) phase_at[k] = std::min(phase_at[k], phase_at[k + 1]);
+      for (int32_t p = 0; p < len; ++p) {
+        const int32_t v = pl.order[ch.begin + p];
+        start[v] = p;
+        int32_t ops[3];
         int k = operands(g, v, ops);
         for (int j = 0; j < k; ++j) {
           const int32_t u = ops[j];
-          if (g.nodes[u].op == XG_OP_INPUT || r.owner[u] < 0 || r.owner[u] == w || got[u]) continue;
-          got[u] = 1;
-          remote[u] = 1;
-          pl.mailbox[(size_t)w * (pl.n_phases + 1) + r.node_phase[u] + 1].push_back(u);
+          last[u] = p;
+          if (start[u] < 0) start[u] = g.nodes[u].op == XG_OP_INPUT ? p : phase_at[r.node_phase[u] + 1];
         }
       }
-    }
-    // values of phase k are copied in phase k + 1; their slots are reused
-    // by values of phase k + 2 on
-    std::vector<std::vector<int32_t>> by_phase(pl.n_phases);
-    for (int32_t v = 0; v < n; ++v)
-      if (remote[v]) by_phase[r.node_phase[v]].push_back(v);
-    // LDS slots up to the allowance, then workspace slots (the same
-    // one-barrier lifetime; a workspace copy is reloaded only by the
-    // mailbox, each wave then keeps its own)
-    std::vector<int32_t> freel, freew;
-    const int64_t cap = po.xch_cap > 0 ? po.xch_cap : INT64_MAX;
-    int64_t ws_loads = 0;
-    for (int32_t ph = 0; ph < pl.n_phases; ++ph) {
-      if (ph >= 2)
-        for (int32_t v : by_phase[ph - 2]) {
-          if (pl.xch_slot[v] >= 0) freel.push_back(pl.xch_slot[v]);
-          else freew.push_back(pl.ws_slot[v]);
-        }
-      for (int32_t v : by_phase[ph]) {
-        if (!freel.empty()) { pl.xch_slot[v] = freel.back(); freel.pop_back(); }
-        else if (pl.n_xch < cap) pl.xch_slot[v] = pl.n_xch++;
-        else if (!freew.empty()) { pl.ws_slot[v] = freew.back(); freew.pop_back(); }
-        else pl.ws_slot[v] = pl.n_ws++;
+      std::vector<int32_t> step(len + 2, 0);
+      for (int32_t v = 0; v < n; ++v)
+        if (last[v] > start[v] && start[v] >= 0) { step[start[v]]++; step[last[v]]--; }
+      int64_t live = 0, over = 0;
+      for (int32_t p = 0; p < len; ++p) {
+        live += step[p];
+        pl.max_live = std::max(pl.max_live, live);
+        const int64_t o = std::max<int64_t>(0, live - po.reg_budget);
+        evicted[w] += std::max<int64_t>(0, o - over);
+        over = o;
+        most_over = std::max(most_over, o);
       }
-    }
-    for (auto& mb : pl.mailbox)
-      for (int32_t u : mb) ws_loads += pl.ws_slot[u] >= 0;
-    // a workspace exchange costs its reader a global load (L2 latency),
-    // far more than an LDS one
-    r.est += 8 * ws_loads / W;
-    // self-check: an operand is an input, computed earlier on the same wave,
-    // or computed by another wave in an earlier phase and exchanged; phases
-    // never decrease along a wave's list
-    for (auto& ch : pl.chunks) {
-      std::vector<char> seen(n, 0);
-      for (int32_t p = ch.begin; p < ch.end; ++p) {
-        const int32_t v = pl.order[p];
-        if (g.nodes[v].op != XG_OP_INPUT) {
-          int32_t ops[2];
-          int k = operands(g, v, ops);
-          for (int j = 0; j < k; ++j) {
-            const int32_t u = ops[j];
-            if (g.nodes[u].op == XG_OP_INPUT || seen[u]) continue;
-            if (!((pl.xch_slot[u] >= 0 || pl.ws_slot[u] >= 0) && r.node_phase[u] < pl.pos_phase[p]))
-              throw std::logic_error("phased plan: operand not available");
-          }
-          if (p > ch.begin && pl.pos_phase[p] < pl.pos_phase[p - 1])
-            throw std::logic_error("phased plan: phases out of order");
-        }
-        seen[v] = 1;
-      }
-    }
-    // plans whose exchanges all fit the LDS come first; workspace
-    // exchanges (and the spills that come with such wide plans) are only
-    // taken when no plan fits
-    const bool lds_only = pl.n_ws == 0;
-    if (lds_only && (!best_lds_only || r.est < best_est)) {
-      best_est = r.est;
-      best_lds_only = true;
-      pl.coop_est = r.est;
-      best = std::move(pl);
-    } else if (!lds_only && !best_lds_only && r.est < best_est) {
-      best_est = r.est;
-      pl.coop_est = r.est;
-      best = std::move(pl);
+      spilled = std::max(spilled, evicted[w]);
     }
   }
-  if (best_est == INT64_MAX) throw std::logic_error(why);
-  return best;
+  // exchange slots (values other waves read) and each wave's mailbox
+  pl.ws_slot.assign(n, -1);
+  pl.xch_slot.assign(n, -1);
+  pl.mailbox.assign((size_t)W * (pl.n_phases + 1), {});
+  std::vector<char> remote(n, 0);
+  for (int w = 0; w < W; ++w) {
+    std::vector<char> got(n, 0);
+    const Chunk& ch = pl.chunks[w];
+    for (int32_t p = ch.begin; p < ch.end; ++p) {
+      const int32_t v = pl.order[p];
+      if (g.nodes[v].op == XG_OP_INPUT) continue;
+      int32_t ops[3];
+      int k = operands(g, v, ops);
+      for (int j = 0; j < k; ++j) {
+        const int32_t u = ops[j];
+        if (g.nodes[u].op == XG_OP_INPUT || r.owner[u] < 0 || r.owner[u] == w || got[u]) continue;
+        got[u] = 1;
+        remote[u] = 1;
+        pl.mailbox[(size_t)w * (pl.n_phases + 1) + r.node_phase[u] + 1].push_back(u);
+      }
+    }
+  }
+  // values of phase k are copied in phase k + 1; their slots are reused
+  // by values of phase k + 2 on
+  std::vector<std::vector<int32_t>> by_phase(pl.n_phases);
+  for (int32_t v = 0; v < n; ++v)
+    if (remote[v]) by_phase[r.node_phase[v]].push_back(v);
+  // LDS slots up to the allowance, then workspace slots (the same
+  // one-barrier lifetime; a workspace copy is reloaded only by the
+  // mailbox, each wave then keeps its own)
+  std::vector<int32_t> freel, freew;
+  const int64_t cap = po.xch_cap > 0 ? po.xch_cap : INT64_MAX;
+  int64_t ws_loads = 0;
+  for (int32_t ph = 0; ph < pl.n_phases; ++ph) {
+    if (ph >= 2)
+      for (int32_t v : by_phase[ph - 2]) {
+        if (pl.xch_slot[v] >= 0) freel.push_back(pl.xch_slot[v]);
+        else freew.push_back(pl.ws_slot[v]);
+      }
+    for (int32_t v : by_phase[ph]) {
+      if (!freel.empty()) { pl.xch_slot[v] = freel.back(); freel.pop_back(); }
+      else if (pl.n_xch < cap) pl.xch_slot[v] = pl.n_xch++;
+      else if (!freew.empty()) { pl.ws_slot[v] = freew.back(); freew.pop_back(); }
+      else pl.ws_slot[v] = pl.n_ws++;
+    }
+  }
+  for (auto& mb : pl.mailbox)
+    for (int32_t u : mb) ws_loads += pl.ws_slot[u] >= 0;
+  // a workspace exchange costs its reader a global load (L2 latency),
+  // far more than an LDS one
+  r.est += 30 * ws_loads / W;
+  // values beyond the register budget are stored and loaded again, in LDS
+  // while the exchange slots leave room, else in the workspace
+  if (po.reg_budget > 0 && po.lds_slots > 0) {
+    const int64_t room = (po.lds_slots - pl.n_xch) / W;
+    r.est += kSpillCost * spilled;
+    if (most_over > room) r.est += kSpillCost * spilled * (most_over - room) / most_over;
+  }
+  // self-check: an operand is an input, computed earlier on the same wave,
+  // or computed by another wave in an earlier phase and exchanged; phases
+  // never decrease along a wave's list
+  for (auto& ch : pl.chunks) {
+    std::vector<char> seen(n, 0);
+    for (int32_t p = ch.begin; p < ch.end; ++p) {
+      const int32_t v = pl.order[p];
+      if (g.nodes[v].op != XG_OP_INPUT) {
+        int32_t ops[3];
+        int k = operands(g, v, ops);
+        for (int j = 0; j < k; ++j) {
+          const int32_t u = ops[j];
+          if (g.nodes[u].op == XG_OP_INPUT || seen[u]) continue;
+          if (!((pl.xch_slot[u] >= 0 || pl.ws_slot[u] >= 0) && r.node_phase[u] < pl.pos_phase[p]))
+            throw std::logic_error("phased plan: operand not available");
+        }
+        if (p > ch.begin && pl.pos_phase[p] < pl.pos_phase[p - 1])
+          throw std::logic_error("phased plan: phases out of order");
+      }
+      seen[v] = 1;
+    }
+  }
+  pl.coop_est = r.est;
+  pl.phase_len = (int32_t)T;
+  return pl;
+}
+
+// Duplicated clusters of up to 1 or 3 cost units, subtrees capped at 8 to 48,
+// both rankings with several weights: the plan with the smallest modelled
+// time, which orders measured times well (4 waves, all settings run: the
+// pendulum's choice 18.4 us, settings 18.4 to 26.7; binary32 15.0 of 15.0 to
+// 18.5; the quadcopter step 43.3 of 43.3 to 48.0).  The settings are planned
+// on several threads; the choice does not depend on their timing.
+static Plan make_phased_plan(const Graph& g, const PlanOptions& po) {
+  std::vector<int64_t> Ts = {std::max(1, po.coop_phase)};
+  if (po.coop_phase == kAutoPhase) Ts = {60, 120, 240, 400};
+  struct Setting { int64_t T, D, S; Policy p; };
+  std::vector<Setting> st;
+  for (Policy p : {Policy{false, 0}, Policy{false, 2}, Policy{true, 1}, Policy{true, 2}, Policy{true, 4}})
+    for (int64_t T : Ts)
+      for (int64_t D : {1, 3})
+        for (int64_t S : {8, 16, 24, 48}) st.push_back({T, D, S, p});
+  std::vector<Plan> pls(st.size());
+  std::vector<std::string> errs(st.size());
+  std::atomic<size_t> next{0};
+  auto work = [&]() {
+    for (size_t i; (i = next++) < st.size();) {
+      try {
+        pls[i] = phased_plan_of(g, po, st[i].T, st[i].D, st[i].S, st[i].p);
+      } catch (const std::exception& e) {
+        errs[i] = e.what();
+      }
+    }
+  };
+  std::vector<std::thread> th;
+  th.reserve(8);
+  const unsigned hw = std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
+  try {
+    for (unsigned k = 1; k < hw; ++k) th.emplace_back(work);
+  } catch (const std::system_error&) {
+    // fewer threads: this one plans what they do not
+  }
+  work();
+  for (auto& t : th) t.join();
+  size_t best = st.size();
+  for (size_t i = 0; i < st.size(); ++i)
+    if (errs[i].empty() && (best == st.size() || pls[i].coop_est < pls[best].coop_est)) best = i;
+  if (best == st.size()) throw std::logic_error(errs[0]);
+  return std::move(pls[best]);
 }
 
 Plan make_plan(const Graph& g, const PlanOptions& po) {
-  if (po.waves > 1 && po.coop_phase > 0) return make_phased_plan(g, po);
+  if (po.waves > 1 && po.coop_phase != 0) return make_phased_plan(g, po);
   if (po.waves > 1) return make_wide_plan(g, po);
   Plan pl;
   std::vector<int32_t> o1 = original_order(g);
@@ -661,7 +755,7 @@ Plan make_plan(const Graph& g, const PlanOptions& po) {
   std::vector<int32_t> last(n, -1), pos(n, -1);
   for (int32_t p = 0; p < L; ++p) {
     pos[pl.order[p]] = p;
-    int32_t ops[2];
+    int32_t ops[3];
     int k = operands(g, pl.order[p], ops);
     for (int j = 0; j < k; ++j) last[ops[j]] = p;
   }
@@ -678,11 +772,18 @@ Plan make_plan(const Graph& g, const PlanOptions& po) {
   }
   // chunk boundaries: at most chunk_ops operations each, cut where the
   // fewest (non-input) values are live in the last quarter of the window
+  // (a fused multiply-add is two of the program's operations)
   const int32_t C = po.chunk_ops > 0 ? po.chunk_ops : INT32_MAX;
+  std::vector<int64_t> done(L + 1, 0);
+  for (int32_t p = 0; p < L; ++p) done[p + 1] = done[p] + 1 + is_fma(g.nodes[pl.order[p]].op);
+  auto after = [&](int32_t from, int64_t ops) {  // first position `ops` operations past `from`
+    return (int32_t)(std::lower_bound(done.begin() + from, done.end(), done[from] + ops) - done.begin());
+  };
   int32_t start = 0;
   while (start < L) {
-    if ((int64_t)L - start <= C) { pl.chunks.push_back({start, L}); break; }
-    int32_t lo = start + std::max(1, (C * 3) / 4), hi = std::min(L, start + C);
+    if (done[L] - done[start] <= C) { pl.chunks.push_back({start, L}); break; }
+    int32_t lo = std::max(start + 1, after(start, (int64_t)C * 3 / 4)), hi = std::min(L, after(start, C));
+    lo = std::min(lo, hi);
     int32_t best = hi, bl = INT32_MAX;
     for (int32_t p = lo; p <= hi; ++p) {
       if (live_after[p - 1] < bl) { bl = live_after[p - 1]; best = p; }
@@ -700,7 +801,7 @@ Plan make_plan(const Graph& g, const PlanOptions& po) {
     // last chunk using each value
     std::vector<int32_t> last_chunk(n, -1);
     for (int32_t p = 0; p < L; ++p) {
-      int32_t ops[2];
+      int32_t ops[3];
       int k = operands(g, pl.order[p], ops);
       for (int j = 0; j < k; ++j) last_chunk[ops[j]] = std::max(last_chunk[ops[j]], chunk_of[p]);
     }

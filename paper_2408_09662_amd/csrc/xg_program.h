@@ -29,6 +29,8 @@ struct ModeState {
   Plan plan;
   EmitStats est;
   int64_t recompute_ops = 0;
+  int64_t cost = 0;     // modelled time of a tile (units of one vector operation)
+  int64_t n_nodes = 0, n_ops = 0;  // SSA values and operations before products join sums
   std::vector<std::string> srcs;
   std::vector<CodeObject> cos;
   bool compiled = false;
@@ -47,7 +49,7 @@ inline size_t ws_bytes_of(int64_t n, int32_t slots, int block, int ipt, size_t e
   return (size_t)tiles * (size_t)slots * (size_t)per * es;
 }
 
-xg_options defaults(const xg_options* o, int dtype);
+xg_options defaults(const xg_options* o, int dtype, bool mixed);
 EmitOptions emit_options_of(const xg_options& o);
 bool check_opts(const xg_options& o, int dtype, std::string& err);
 
@@ -58,6 +60,15 @@ struct xg_program {
   xg_options opt;   // forward evaluation (mode 0)
   xg_options aopt;  // adjoint evaluations (modes 1 and 2); the load options until tuned
   xg::ModeState m[3];
+  // A mode whose plan the caller left to the library (every launch option
+  // 0, not tuned) has a second plan for launches with too few tiles to fill
+  // the chip (pick_few).  Both plans of a mode round alike, so which one
+  // runs shows in the time only.
+  bool library_plan[3] = {false, false, false};
+  int few_state[3] = {0, 0, 0};  // 0 not formed yet, 1 formed, -1 none
+  int64_t few_most[3] = {0, 0, 0};  // most instances that run it
+  xg_options few_opt[3];
+  xg::ModeState few[3];
   std::mutex mu;
   // HIP graphs whose kernel nodes run this program's loaded code.  While
   // any exists the code stays loaded: re-planning (autotuning) is refused
@@ -67,17 +78,26 @@ struct xg_program {
   bool free_pending = false;
 };
 
-// Options a mode is planned and launched with.
-inline const xg_options& mode_opt(const xg_program* p, int mode) { return mode == 0 ? p->opt : p->aopt; }
+// Options a mode is planned and launched with (`few`: its plan for few tiles).
+inline const xg_options& mode_opt(const xg_program* p, int mode, bool few = false) {
+  return few ? p->few_opt[mode] : mode == 0 ? p->opt : p->aopt;
+}
+inline xg::ModeState& mode_state(xg_program* p, int mode, bool few) { return few ? p->few[mode] : p->m[mode]; }
 
 namespace xg {
-bool plan_mode(xg_program* p, int mode, std::string& err);
+bool plan_mode(xg_program* p, int mode, std::string& err, bool few = false);
 // hiprtc and host checks only (no device); *code as for compile_mode
-bool build_code(xg_program* p, int mode, std::string& err, xg_status* code = nullptr);
+bool build_code(xg_program* p, int mode, std::string& err, xg_status* code = nullptr, bool few = false);
 // + load on the current device; on failure *code (if given) says why:
 // XG_ECOMPILE, XG_EUNSUPPORTED (a kernel that cannot be launched as
 // planned) or XG_EDEVICE
-bool compile_mode(xg_program* p, int mode, std::string& err, xg_status* code = nullptr);
+bool compile_mode(xg_program* p, int mode, std::string& err, xg_status* code = nullptr, bool few = false);
+// Whether n instances of `mode` run the plan for few tiles (formed and
+// planned by this call if need be; the caller holds p->mu)
+bool pick_few(xg_program* p, int mode, int64_t n);
+// Launch options of the library's own plans, before any rule on n: the
+// values xg_autotune's candidates are spread around
+constexpr int kTuneRegs64 = 112, kTuneRegs32 = 200;
 void reset_mode(xg_program* p, int mode);  // drain, unload, forget the plan
 void destroy_program(xg_program* p);       // unload every mode and delete
 // xg_eval_adjoint on the kernels already loaded on the current device, with
