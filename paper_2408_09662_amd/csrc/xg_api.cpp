@@ -141,6 +141,11 @@ bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
   // the workspace costs an L2 round trip
   po.lds_slots = kLdsSpillBytes / (64 * (M.g.dtype == XG_F32 ? 4 : 8));
   po.xch_cap = po.lds_slots * 7 / 8;
+  // (spill regions held to less than half of the LDS ask for two tiles on a
+  // CU: the exchanges stay within the other's reach too)
+  const int64_t spill_slots = (int64_t)opt.lds_slots * std::max(1, opt.waves);
+  const int64_t half_slots = 160 * 1024 / 2 / (64 * (M.g.dtype == XG_F32 ? 4 : 8));
+  if (spill_slots < half_slots) po.xch_cap = std::max<int64_t>(16, half_slots - spill_slots);
   po.reg_budget = opt.reg_budget;
   try {
     M.plan = make_plan(M.g, po);
