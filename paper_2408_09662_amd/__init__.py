@@ -92,9 +92,25 @@ def _from_workload(prog):
                 instr=instr.reshape(-1, 4), prec=prec)
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
+
+
+_arrays = {}  # array types by length (ctypes builds a new type otherwise)
+
+
+def _array_types(k):
+    t = _arrays.get(k)
+    if t is None:
+        t = _arrays[k] = (ctypes.c_void_p * k, ctypes.c_int64 * k)
+    return t
 
 
 def _stream_handle(stream):
@@ -117,8 +133,10 @@ def _ptrs(tensors, n, dtype, nnz, what="argument"):
     k = len(nnz)
     if len(tensors) != k:
         raise XgError(f"expected {k} {what} tensors, got {len(tensors)}")
-    P = (ctypes.c_void_p * max(k, 1))()
-    L = (ctypes.c_int64 * max(k, 1))()
+    VP, I64 = _array_types(max(k, 1))
+    P = VP()
+    L = I64()
+    Tensor = torch.Tensor
     for i, t in enumerate(tensors):
         if t is None:
             if nnz[i] != 0:
@@ -126,16 +144,17 @@ def _ptrs(tensors, n, dtype, nnz, what="argument"):
             P[i] = None
             L[i] = n
             continue
-        if not isinstance(t, torch.Tensor) or not t.is_cuda:
+        if not isinstance(t, Tensor) or not t.is_cuda:
             raise XgError(f"{what} {i} must be a CUDA (HIP) tensor")
         if t.dtype != dtype:
             raise XgError(f"{what} {i}: dtype {t.dtype} does not match the program's {dtype}")
-        if t.dim() != 2 or t.stride(1) != 1 or t.shape[1] < n:
+        shape, stride = t.shape, t.stride()
+        if len(shape) != 2 or stride[1] != 1 or shape[1] < n:
             raise XgError(f"{what} {i} must be 2-D (nnz, N >= {n}) with unit stride over instances")
-        if t.shape[0] != nnz[i]:
-            raise XgError(f"{what} {i} has {t.shape[0]} rows; the program's argument has {nnz[i]}")
+        if shape[0] != nnz[i]:
+            raise XgError(f"{what} {i} has {shape[0]} rows; the program's argument has {nnz[i]}")
         P[i] = t.data_ptr()
-        L[i] = t.stride(0) if t.shape[0] > 1 else max(n, t.shape[1])
+        L[i] = stride[0] if shape[0] > 1 else max(n, shape[1])
     return P, L
 
 
@@ -194,6 +213,16 @@ class Program:
         torch = _torch()
         return torch.float64 if self.dtype == "f64" else torch.float32
 
+    def _bytes_for(self, n: int, mode: int) -> int:
+        """workspace_bytes, kept per plan (autotuning replaces self._ws)."""
+        key = ("bytes", mode, n)
+        nb = self._ws.get(key)
+        if nb is None:
+            if len(self._ws) > 64:  # many counts: start over (workspaces stay)
+                self._ws = {k: v for k, v in self._ws.items() if k[0] != "bytes"}
+            nb = self._ws[key] = self.workspace_bytes(n, mode)
+        return nb
+
     def info(self, mode: int = 0) -> dict:
         inf = _abi.Info()
         _abi.check(lib().xg_program_info(self._h, mode, ctypes.byref(inf)))
@@ -219,7 +248,7 @@ class Program:
 
     def workspace(self, n: int, mode: int = 0):
         """A cached device workspace (torch uint8 tensor) or None."""
-        nb = self.workspace_bytes(n, mode)
+        nb = self._bytes_for(n, mode)
         if nb == 0:
             return None
         key = (mode, _torch().cuda.current_device())
@@ -230,8 +259,8 @@ class Program:
         return ws
 
     def alloc_outputs(self, n: int):
-        torch = _torch()
-        return [torch.empty((k, n), dtype=self.torch_dtype, device="cuda") for k in self.nnz_out]
+        empty, dt = _torch().empty, self.torch_dtype
+        return [empty((k, n), dtype=dt, device="cuda") for k in self.nnz_out]
 
     def _n_of(self, tensors, n):
         if n is not None:
@@ -248,12 +277,14 @@ class Program:
         n = self._n_of(list(inputs) + list(outputs or []), n)
         if outputs is None:
             outputs = self.alloc_outputs(n)
-        pi, li = _ptrs(inputs, n, self.torch_dtype, self.nnz_in, "input")
-        po, lo = _ptrs(outputs, n, self.torch_dtype, self.nnz_out, "output")
+        dt = self.torch_dtype
+        pi, li = _ptrs(inputs, n, dt, self.nnz_in, "input")
+        po, lo = _ptrs(outputs, n, dt, self.nnz_out, "output")
         ws = workspace if workspace is not None else self.workspace(n, 0)
-        _abi.check(lib().xg_eval(self._h, n, pi, li, po, lo,
-                                 ctypes.c_void_p(ws.data_ptr() if ws is not None else 0),
-                                 _stream_handle(stream)))
+        st = lib().xg_eval(self._h, n, pi, li, po, lo, ws.data_ptr() if ws is not None else None,
+                           _stream_handle(stream))
+        if st != 0:
+            _abi.check(st)
         return outputs
 
     def bind_eval(self, inputs, outputs, n=None, stream=None, workspace=None):
