@@ -164,6 +164,17 @@ bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
   if (mode != 0 && p->library_plan[mode]) {
     if (p->g.dtype == XG_F32) eo.reg_budget = kTuneRegs32;
     else eo.reg_budget = !long_adjoint ? kTuneRegs64 : M.plan.max_live > 300 ? 168 : 130;
+    // A budget that holds every value leaves a source without reloads, hence
+    // without the fences that keep the compiler near the planned order: it
+    // then holds far more than the plan and spills to scratch (4 links,
+    // binary64, 124 live, budget 112: 1,464 B of scratch, 54 us at 29,140
+    // instances; none at 93 and 27 us.  Binary32, where a value is one
+    // register: 496 B and 20.9 us at 1,000 with budget 200, 16.7 us at 108,
+    // 18.1 at 100).
+    if (p->g.dtype == XG_F32 && M.plan.max_live >= 110)
+      eo.reg_budget = (int)std::min<int64_t>(eo.reg_budget, M.plan.max_live * 7 / 8);
+    if (p->g.dtype != XG_F32 && M.plan.max_live >= 80)
+      eo.reg_budget = (int)std::min<int64_t>(eo.reg_budget, M.plan.max_live * 3 / 4);
   }
   char prefix[64];
   std::snprintf(prefix, sizeof prefix, "xg_m%d", mode);
