@@ -364,6 +364,7 @@ std::vector<xg_options> tune_candidates(xg_program* p, int64_t n, int mode) {
     for (int rb : {rb0 * 3 / 4, rb0, rb0 * 4 / 3, rb0 * 5 / 3, rb0 * 2, rb0 * 16 / 7, rb0 * 5 / 2})
       for (int pf : {24, 64}) {
         if (pf != 24 && rb != rb0 && rb != rb0 * 5 / 3) continue;
+        if (mode != 0 && rb > rb0 * 2) continue;  // (scratch: see below)
         xg_options o = base;
         o.reg_budget = rb;
         o.prefetch = pf;
@@ -413,21 +414,21 @@ std::vector<xg_options> tune_candidates(xg_program* p, int64_t n, int mode) {
   // reverse sweep against the number of cuts (and levels of recomputation);
   // the fan-out trades states held per level against recomputation
   if (mode != 0) {
-    // (the pendulum's fused adjoint at 65,536 instances, 500-operation
-    // leaves: 0.255 ms at 5/3 of the load setting, 0.28-0.29 at twice it)
-    for (int rb : {rb0 * 5 / 3, rb0 * 2, rb0 * 16 / 7})
-      for (int sg : {base.adj_seg_ops * 3 / 5, base.adj_seg_ops, base.adj_seg_ops * 2})
-        for (int fo : {2, 4}) {
-          xg_options b = o;
-          b.reg_budget = rb;
-          b.adj_seg_ops = std::max(50, sg);
-          b.adj_fanout = fo;
-          // one kernel per adjoint for binary64 programs; binary32 ones keep
-          // their chunks (a single 68,000-statement binary32 kernel takes
-          // hiprtc about ten minutes; the one-kernel candidate above stays)
-          if (one_kernel && p->g.dtype != XG_F32) b.chunk_ops = 5 * base.chunk_ops;
-          cands.push_back(b);
-        }
+    // (the pendulum's fused adjoint at 65,536 instances as one kernel: 245 us
+    // at 5/3 of the load setting, 255 with 500-operation leaves; fan-out 4
+    // takes 304, and budgets past twice the setting go to scratch, so they
+    // are not tried)
+    for (int rb : {rb0 * 3 / 2, rb0 * 5 / 3, rb0 * 2})
+      for (int sg : {base.adj_seg_ops, base.adj_seg_ops * 2}) {
+        xg_options b = o;
+        b.reg_budget = rb;
+        b.adj_seg_ops = std::max(50, sg);
+        // one kernel per adjoint for binary64 programs; binary32 ones keep
+        // their chunks (a single 68,000-statement binary32 kernel takes
+        // hiprtc minutes; the one-kernel candidate above stays)
+        if (one_kernel && p->g.dtype != XG_F32) b.chunk_ops = 5 * base.chunk_ops;
+        cands.push_back(b);
+      }
   }
   // cooperative tiles, when few tiles leave SIMDs idle and the program is
   // wide (operations per dependency level) enough to split
