@@ -147,6 +147,7 @@ bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
   const int64_t half_slots = 160 * 1024 / 2 / (64 * (M.g.dtype == XG_F32 ? 4 : 8));
   if (spill_slots < half_slots) po.xch_cap = std::max<int64_t>(16, half_slots - spill_slots);
   po.reg_budget = opt.reg_budget;
+  po.transfers_first = M.transfers_first;
   try {
     M.plan = make_plan(M.g, po);
   } catch (const std::logic_error& e) {
@@ -246,19 +247,35 @@ static void form_few(xg_program* p, int mode) {
   if (B.n_ops < 100 || B.n_ops > 60000) return;
   ModeState best;
   xg_options best_o = o;
-  for (int W : {4, 2}) {
+  // A plan's spills add to its modelled time, workspace accesses most of all:
+  // an LDL^T solve of 48 x 48 at 10,000 instances takes 247 us with 32,600 +
+  // 16,195 accesses on 4 waves, 171 with 35,500 + 8,451; the MPC on 2 waves
+  // 125 us at 4,096 instances and 565 at 65,536 with 77,900 + 4,709, 111 and
+  // 536 with 79,500 + 4,318, 132 and 649 with 77,200 + 6,015.  LDS accesses
+  // weigh little (at 2 each the quadcopter's 22,730 + 8,288 on 4 waves lose to
+  // 28,234 + 3,900 on 2: 20 steps of 10,000 instances 805 us against 1,042).
+  auto score = [](const ModeState& M) { return M.plan.coop_est + 12 * M.est.ws_ops + M.est.lds_ops / 2; };
+  auto consider = [&](int W, int phase, bool transfers_first) {
     o.waves = W;
-    o.coop_phase = kAutoPhase;
+    o.coop_phase = phase;
     o.lds_slots = (int32_t)(kLdsSpillBytes / (64 * W * es));
     p->few[0] = ModeState();
+    p->few[0].transfers_first = transfers_first;
     p->few_opt[0] = o;
-    if (!plan_mode(p, 0, err, true)) continue;
-    if (!best.planned || p->few[0].plan.coop_est < best.plan.coop_est) {
+    if (!plan_mode(p, 0, err, true)) return;
+    if (!best.planned || score(p->few[0]) < score(best)) {
       best = std::move(p->few[0]);
       best_o = o;
       best_o.coop_phase = best.plan.phase_len;
     }
-  }
+  };
+  for (int W : {4, 2}) consider(W, kAutoPhase, false);
+  // Plans that spill to the workspace anyway: also those that rank a value's
+  // wave by transfers alone, which hold fewer values on two waves at once
+  // (others gain nothing from them and would only plan for longer).
+  if (best.planned && best.est.ws_ops > 0)
+    for (int W : {4, 2})
+      for (int phase : {240, 400}) consider(W, phase, true);
   p->few[0] = std::move(best);
   if (!p->few[0].planned) return;
   p->few_opt[0] = best_o;

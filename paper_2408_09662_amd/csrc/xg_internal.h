@@ -122,6 +122,7 @@ struct PlanOptions {
   int64_t xch_cap = 0; // most LDS exchange slots the phased plan may use
   int64_t lds_slots = 0; // LDS slots of 64 lanes in all (exchanges and spills)
   int reg_budget = 0;  // values a wave holds in registers
+  bool transfers_first = false;  // phased plan: rank choices by what they transfer
 };
 // coop_phase of a phased plan that chooses its phases' length itself
 constexpr int kAutoPhase = -1;

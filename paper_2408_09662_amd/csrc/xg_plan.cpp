@@ -705,7 +705,11 @@ static Plan make_phased_plan(const Graph& g, const PlanOptions& po) {
   if (po.coop_phase == kAutoPhase) Ts = {60, 120, 240, 400};
   struct Setting { int64_t T, D, S; Policy p; };
   std::vector<Setting> st;
-  for (Policy p : {Policy{false, 0}, Policy{false, 2}, Policy{true, 1}, Policy{true, 2}, Policy{true, 4}})
+  // (a weight of 1,000 ranks by transfers alone: fewer values are held by two
+  // waves, for programs that spill much)
+  std::vector<Policy> policies = {Policy{false, 0}, Policy{false, 2}, Policy{true, 1}, Policy{true, 2}, Policy{true, 4}};
+  if (po.transfers_first) policies = {Policy{false, 1000}};
+  for (Policy p : policies)
     for (int64_t T : Ts)
       for (int64_t D : {1, 3})
         for (int64_t S : {8, 16, 24, 48}) st.push_back({T, D, S, p});

@@ -29,6 +29,7 @@ struct ModeState {
   Plan plan;
   EmitStats est;
   int64_t recompute_ops = 0;
+  bool transfers_first = false;  // phased plan ranked by transfers (form_few)
   int64_t cost = 0;     // modelled time of a tile (units of one vector operation)
   int64_t n_nodes = 0, n_ops = 0;  // SSA values and operations before products join sums
   std::vector<std::string> srcs;

@@ -45,3 +45,18 @@ def test_workspace_of_a_larger_count_serves_a_smaller(key, most, n):
     x = [torch.from_numpy(t).cuda() for t in configs.ITEMS[key].make_inputs(n)]
     ws = torch.empty(max(p.workspace_bytes(most), 8), dtype=torch.uint8, device="cuda")
     assert torch.equal(p.eval(x, workspace=ws)[0], p.eval(x)[0])
+
+
+@pytest.mark.parametrize("key,n", [("mpc", 65), ("ldl48", 130)])
+def test_plans_ranked_by_transfers(key, n):
+    """Programs that spill to the workspace: their plan for few tiles against
+    one wave per tile, bit by bit, and the oracle."""
+    import paper_2408_09662_amd as xg
+    path = configs.program_path(key)
+    xs = configs.ITEMS[key].make_inputs(n)
+    x = [torch.from_numpy(t).cuda() for t in xs]
+    a, b = xg.Program(path).eval(x), xg.Program(path, reg_budget=112).eval(x)
+    torch.cuda.synchronize()
+    assert all(torch.equal(p, q) for p, q in zip(a, b)), key
+    ref = OProg(path).evaluate(xs, 64, threads=8)
+    assert parity.max_err([t.cpu().numpy() for t in a], ref) <= parity.TOL_F64, key
