@@ -177,6 +177,7 @@ bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
     if (p->g.dtype != XG_F32 && M.plan.max_live >= 80)
       eo.reg_budget = (int)std::min<int64_t>(eo.reg_budget, M.plan.max_live * 3 / 4);
   }
+  M.eo = eo;
   char prefix[64];
   std::snprintf(prefix, sizeof prefix, "xg_m%d", mode);
   if (M.plan.phased) M.srcs = emit_phased(M.g, M.plan, eo, prefix, &M.est);

@@ -102,8 +102,7 @@ std::string build_batch_source(xg_batch* b, std::string& err) {
   // per-program types and argument structs
   for (int k = 0; k < K; ++k) {
     const Graph& g = b->progs[k]->m[0].g;
-    EmitOptions eo = emit_options_of(b->progs[k]->opt);
-    s << "namespace P" << k << " {\n" << emit_preamble(g, eo);
+    s << "namespace P" << k << " {\n" << emit_preamble(g, b->progs[k]->m[0].eo);
     s << "struct Args { long long n; T* ws;";
     for (size_t a = 0; a < g.nnz_in.size(); ++a) s << " const T* in" << a << "; long long ldi" << a << ";";
     for (size_t a = 0; a < g.nnz_out.size(); ++a) s << " T* out" << a << "; long long ldo" << a << ";";
@@ -116,7 +115,9 @@ std::string build_batch_source(xg_batch* b, std::string& err) {
   for (int k = 0; k < K; ++k) {
     ModeState& M = b->progs[k]->m[0];
     const Graph& g = M.g;
-    EmitOptions eo = emit_options_of(b->progs[k]->opt);
+    // emitted as the plan was (its register budget may be below the program's
+    // option): the tile's LDS and workspace are sized from M.est
+    const EmitOptions& eo = M.eo;
     std::ostringstream pro;
     pro << "  const P" << k << "::Args& A = XG_BARGS->a" << k << ";\n";
     pro << "  const long long n = A.n; T* __restrict__ ws = A.ws;\n";
@@ -129,7 +130,6 @@ std::string build_batch_source(xg_batch* b, std::string& err) {
     s << contract_pragma(b->progs[0]->opt.strict != 0) << contract_end(b->progs[0]->opt.strict != 0, g);
     s << "namespace P" << k << " {\n";
     if (M.plan.phased) {
-      eo.waves = M.plan.waves;
       PhasedParts pp = emit_phased_parts(g, M.plan, eo, "xg_lds_raw");
       if (pp.ns != M.ws_slots() || pp.lds_bytes > (int64_t)lds_bytes) {
         err = "batch: phased plan differs from the program's";
@@ -140,17 +140,22 @@ std::string build_batch_source(xg_batch* b, std::string& err) {
       continue;
     }
     if (M.plan.waves > 1) {
-      eo.waves = M.plan.waves;
       WideParts wp = emit_wide_parts(g, M.plan, eo, pro.str(), "xg_lds_raw", "g");
-      if (wp.ns != M.ws_slots()) { err = "batch: cooperative plan differs from the program's"; return ""; }
+      if (wp.ns != M.ws_slots() || wp.st.lds_slots > M.est.lds_slots) { err = "batch: cooperative plan differs from the program's"; return ""; }
       s << wp.funcs;
       s << "__device__ __forceinline__ void run(long long ibase, int xg_w) {\n" << wp.body << "}\n}\n";
       continue;
     }
     if (lds_bytes) pro << "  lT* lds = (lT*)xg_lds_raw;\n";
-    for (size_t c = 0; c < M.plan.chunks.size(); ++c)
-      s << emit_device_chunk(g, M.plan, (int)c, eo, "c" + std::to_string(c), pro.str(), nullptr,
+    for (size_t c = 0; c < M.plan.chunks.size(); ++c) {
+      EmitStats st;
+      s << emit_device_chunk(g, M.plan, (int)c, eo, "c" + std::to_string(c), pro.str(), &st,
                              M.plan.n_ws, M.ws_slots());
+      if (st.extra_ws > M.est.extra_ws || st.lds_slots > M.est.lds_slots) {
+        err = "batch: a kernel's spills differ from the program's plan";
+        return "";
+      }
+    }
     s << "__device__ __forceinline__ void run(long long ibase, int) {";
     for (size_t c = 0; c < M.plan.chunks.size(); ++c) s << " c" << c << "(ibase);";
     s << " }\n}\n";
@@ -551,6 +556,19 @@ xg_status batch_make(const std::vector<xg_program*>& progs, std::unique_ptr<xg_b
   out = std::move(b);
   return XG_OK;
 }
+
+}  // namespace
+
+namespace xg {
+xg_status batch_source(const std::vector<xg_program*>& progs, std::string& src) {
+  std::unique_ptr<xg_batch> b;
+  const xg_status st = batch_make(progs, b);
+  if (st == XG_OK) src = b->src;
+  return st;
+}
+}  // namespace xg
+
+namespace {
 
 void reset_modes(xg_program* p) {
   for (int m = 0; m < 3; ++m) reset_mode(p, m);

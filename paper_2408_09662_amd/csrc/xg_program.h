@@ -32,6 +32,7 @@ struct ModeState {
   bool transfers_first = false;  // phased plan ranked by transfers (form_few)
   int64_t cost = 0;     // modelled time of a tile (units of one vector operation)
   int64_t n_nodes = 0, n_ops = 0;  // SSA values and operations before products join sums
+  EmitOptions eo;       // what the sources were emitted with (est counts that emission)
   std::vector<std::string> srcs;
   std::vector<CodeObject> cos;
   bool compiled = false;
@@ -99,6 +100,8 @@ bool pick_few(xg_program* p, int mode, int64_t n);
 // Launch options of the library's own plans, before any rule on n: the
 // values xg_autotune's candidates are spread around
 constexpr int kTuneRegs64 = 112, kTuneRegs32 = 200;
+// The source of the persistent kernel over progs (host only: nothing is compiled)
+xg_status batch_source(const std::vector<xg_program*>& progs, std::string& src);
 void reset_mode(xg_program* p, int mode);  // drain, unload, forget the plan
 void destroy_program(xg_program* p);       // unload every mode and delete
 // xg_eval_adjoint on the kernels already loaded on the current device, with

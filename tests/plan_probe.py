@@ -1,0 +1,33 @@
+"""tests/native/plan_probe.cpp, built on first use and bound with ctypes."""
+
+import ctypes
+import os
+import subprocess
+import tempfile
+
+import paper_2408_09662_amd as xg
+from paper_2408_09662_amd import build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+_lib = None
+
+
+def lib():
+    global _lib
+    if _lib is None:
+        so = os.path.join(tempfile.mkdtemp(prefix="xg_probe"), "plan_probe.so")
+        libdir = os.path.dirname(xg._abi.LIB_PATH)
+        rocm = os.path.dirname(os.path.dirname(build.HIPCC))
+        subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                        "-I", os.path.join(rocm, "include"), "-I", os.path.join(ROOT, "include"),
+                        "-I", os.path.join(libdir, "csrc"), os.path.join(ROOT, "tests", "native", "plan_probe.cpp"),
+                        "-o", so, "-L", libdir, "-l:libxg.so", f"-Wl,-rpath,{libdir}"], check=True)
+        xg.lib()  # (libxg.so is in the process before what links against it)
+        _lib = ctypes.CDLL(so)
+    return _lib
+
+
+def batch_source(programs, path):
+    arr = (ctypes.c_void_p * len(programs))(*[p._h.value for p in programs])
+    xg._abi.check(lib().probe_batch_source(arr, len(programs), os.fsencode(path)))
+    return open(path).read()
