@@ -199,7 +199,8 @@ class Program:
         h = ctypes.c_void_p()
         _abi.check(L.xg_program_load(ctypes.byref(desc), ctypes.byref(opts), ctypes.byref(h)))
         self._h = h
-        self._ws = {}
+        self._ws = {}  # workspaces by (mode, device)
+        self._bare = False  # the forward plans need no workspace, whatever the count
 
     def __del__(self):
         h = getattr(self, "_h", None)
@@ -212,16 +213,6 @@ class Program:
     def torch_dtype(self):
         torch = _torch()
         return torch.float64 if self.dtype == "f64" else torch.float32
-
-    def _bytes_for(self, n: int, mode: int) -> int:
-        """workspace_bytes, kept per plan (autotuning replaces self._ws)."""
-        key = ("bytes", mode, n)
-        nb = self._ws.get(key)
-        if nb is None:
-            if len(self._ws) > 64:  # many counts: start over (workspaces stay)
-                self._ws = {k: v for k, v in self._ws.items() if k[0] != "bytes"}
-            nb = self._ws[key] = self.workspace_bytes(n, mode)
-        return nb
 
     def info(self, mode: int = 0) -> dict:
         inf = _abi.Info()
@@ -248,7 +239,7 @@ class Program:
 
     def workspace(self, n: int, mode: int = 0):
         """A cached device workspace (torch uint8 tensor) or None."""
-        nb = self._bytes_for(n, mode)
+        nb = self.workspace_bytes(n, mode)  # (asked each time: tuning changes it)
         if nb == 0:
             return None
         key = (mode, _torch().cuda.current_device())
@@ -280,10 +271,16 @@ class Program:
         dt = self.torch_dtype
         pi, li = _ptrs(inputs, n, dt, self.nnz_in, "input")
         po, lo = _ptrs(outputs, n, dt, self.nnz_out, "output")
-        ws = workspace if workspace is not None else self.workspace(n, 0)
+        ws, bare = workspace, workspace is None and self._bare
+        if ws is None and not bare:
+            ws = self.workspace(n, 0)
+            self._bare = ws is None and n > 0
         st = lib().xg_eval(self._h, n, pi, li, po, lo, ws.data_ptr() if ws is not None else None,
                            _stream_handle(stream))
         if st != 0:
+            if bare:  # tuned since, perhaps: the library refuses a missing workspace
+                self._bare = False
+                return self.eval(inputs, outputs, n, stream)
             _abi.check(st)
         return outputs
 
