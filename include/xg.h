@@ -202,7 +202,8 @@ xg_status xg_workspace_bytes(xg_program* p, int64_t n, int32_t mode, size_t* byt
 
 /* Compile (if not yet compiled) the kernels of `mode` for the current
  * device, both plans' where the library chose them.  Optional: evaluation
- * compiles on first use (a capturing stream runs what is loaded). */
+ * compiles on first use, after which a capturing stream finds code for every
+ * count (the plan that fills the chip where only that one is loaded). */
 xg_status xg_compile(xg_program* p, int32_t mode);
 
 /* Generate and compile the code objects of `mode` into the on-disk cache

@@ -348,6 +348,13 @@ static bool check_mode_code(xg_program* p, int mode, std::string& err, bool few)
   return true;
 }
 
+static void count_compiled(ModeState& M) {
+  M.compile_ms = 0;
+  M.cache_hits = 0;
+  for (auto& co : M.cos) { M.compile_ms += co.compile_ms; M.cache_hits += co.cache_hit; }
+  M.compiled = true;
+}
+
 bool build_code(xg_program* p, int mode, std::string& err, xg_status* code, bool few) {
   xg_status dummy;
   if (!code) code = &dummy;
@@ -359,10 +366,7 @@ bool build_code(xg_program* p, int mode, std::string& err, xg_status* code, bool
     if (!compile_many(M.srcs, base_compile_options(mode_opt(p, mode).strict != 0), M.cos, err,
                       mode_opt(p, mode).verbose != 0))
       return false;
-    M.compile_ms = 0;
-    M.cache_hits = 0;
-    for (auto& co : M.cos) { M.compile_ms += co.compile_ms; M.cache_hits += co.cache_hit; }
-    M.compiled = true;
+    count_compiled(M);
   }
   *code = XG_EUNSUPPORTED;
   return check_mode_code(p, mode, err, few);
@@ -408,16 +412,74 @@ bool compile_mode(xg_program* p, int mode, std::string& err, xg_status* code, bo
   return true;
 }
 
-}  // namespace xg
-
-namespace {
-
-const DevMod* devmod(ModeState& M) {
+static const DevMod* devmod(ModeState& M) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return nullptr;
   for (auto& d : M.devs) if (d.device == dev) return &d;
   return nullptr;
 }
+
+// A plan for few tiles that cannot be built is dropped: the other plan runs
+// every count.
+bool build_plans(xg_program* p, int mode, std::string& err, xg_status* code) {
+  *code = XG_EINVAL;
+  if (!plan_mode(p, mode, err)) return false;
+  (void)pick_few(p, mode, 1);  // forms the plan for few tiles
+  ModeState &B = p->m[mode], &F = p->few[mode];
+  const xg_options& opt = mode_opt(p, mode);
+  if (p->few_state[mode] == 1 && !B.compiled && !F.compiled) {  // both plans' sources at once
+    std::vector<std::string> srcs = B.srcs;
+    srcs.insert(srcs.end(), F.srcs.begin(), F.srcs.end());
+    std::vector<CodeObject> cos;
+    std::string e;
+    if (compile_many(srcs, base_compile_options(opt.strict != 0), cos, e, opt.verbose != 0)) {
+      F.cos.assign(cos.begin() + B.srcs.size(), cos.end());
+      cos.resize(B.srcs.size());
+      B.cos.swap(cos);
+      count_compiled(B);
+      count_compiled(F);
+    }  // else: each alone, to tell which fails
+  }
+  if (!build_code(p, mode, err, code)) return false;
+  std::string e;
+  if (p->few_state[mode] == 1 && !build_code(p, mode, e, nullptr, true)) {
+    if (opt.verbose) std::fprintf(stderr, "[xg] mode %d: no plan for few tiles: %s\n", mode, e.c_str());
+    F = ModeState();
+    p->few_state[mode] = -1;
+  }
+  return true;
+}
+
+bool load_plans(xg_program* p, int mode, std::string& err, xg_status* code) {
+  if (!build_plans(p, mode, err, code)) return false;
+  if (!compile_mode(p, mode, err, code)) return false;
+  std::string e;  // (launches fall back to the plan just loaded)
+  if (p->few_state[mode] == 1) (void)compile_mode(p, mode, e, nullptr, true);
+  return true;
+}
+
+bool load_for(xg_program* p, int mode, int64_t n, void* stream, bool& few, std::string& err, xg_status* code) {
+  few = pick_few(p, mode, n);
+  if (!few || devmod(p->few[mode])) return compile_mode(p, mode, err, code, few);
+  // The plan that fills the chip is loaded before or with the one for few
+  // tiles, so after one evaluation of any count a capturing stream finds
+  // code for every count; it loads no module.
+  if (devmod(p->m[mode])) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream, &cs) != hipSuccess) (void)hipGetLastError();
+    if (cs != hipStreamCaptureStatusNone) {
+      few = false;
+      return true;
+    }
+  }
+  if (!load_plans(p, mode, err, code)) return false;
+  few = p->few_state[mode] == 1 && devmod(p->few[mode]);
+  return true;
+}
+
+}  // namespace xg
+
+namespace {
 
 size_t esize(const Graph& g) { return g.dtype == XG_F32 ? 4 : 8; }
 
@@ -457,14 +519,7 @@ xg_status launch_mode(xg_program* p, int mode, int64_t n, const std::vector<cons
   {
     std::lock_guard<std::mutex> lk(p->mu);
     xg_status code = XG_OK;
-    few = pick_few(p, mode, n);
-    if (few && !devmod(p->few[mode]) && devmod(p->m[mode])) {
-      // modules are not loaded while a stream captures: what is loaded runs
-      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-      if (hipStreamIsCapturing((hipStream_t)stream, &cs) != hipSuccess) (void)hipGetLastError();
-      if (cs != hipStreamCaptureStatusNone) few = false;
-    }
-    if (!compile_mode(p, mode, err, &code, few)) {
+    if (!load_for(p, mode, n, stream, few, err, &code)) {
       set_error(err);
       return code;
     }
@@ -659,7 +714,8 @@ xg_status xg_program_load(const xg_program_desc* desc, const xg_options* opts, x
     if (!check_opts(p->opt, desc->dtype, err)) { set_error(err); return XG_EINVAL; }
     p->aopt = p->opt;
     if (p->opt.eager) {
-      if (!plan_mode(p.get(), 0, err) || !compile_mode(p.get(), 0, err)) {
+      xg_status code = XG_OK;
+      if (!load_plans(p.get(), 0, err, &code)) {
         set_error(err);
         return XG_ECOMPILE;
       }
@@ -764,19 +820,7 @@ xg_status xg_compile(xg_program* p, int32_t mode) {
   std::lock_guard<std::mutex> lk(p->mu);
   try {
     xg_status code = XG_OK;
-    const bool few = pick_few(p, mode, 1);  // the plan of the smallest launches too
-    if (few) {  // both plans' sources compile at once
-      std::vector<std::string> srcs = p->m[mode].srcs;
-      srcs.insert(srcs.end(), p->few[mode].srcs.begin(), p->few[mode].srcs.end());
-      std::vector<CodeObject> cos;
-      if (!compile_many(srcs, base_compile_options(mode_opt(p, mode).strict != 0), cos, err,
-                        mode_opt(p, mode).verbose != 0)) {
-        set_error(err);
-        return XG_ECOMPILE;
-      }
-    }
-    if (!compile_mode(p, mode, err, &code)) { set_error(err); return code; }
-    if (few && !compile_mode(p, mode, err, &code, true)) { set_error(err); return code; }
+    if (!load_plans(p, mode, err, &code)) { set_error(err); return code; }
   } catch (const std::exception& e) { set_error(e.what()); return XG_ENOMEM; }
   return XG_OK;
 }

@@ -704,8 +704,8 @@ xg_status xg_graph_capture_eval(xg_program* p, int64_t n, const void* const* d_i
     std::string err;
     std::lock_guard<std::mutex> lk(p->mu);
     xg_status code = XG_OK;
-    // no module loads while capturing
-    if (!compile_mode(p, 0, err, &code, pick_few(p, 0, n))) { set_error(err); return code; }
+    bool few;  // no module loads while capturing
+    if (!load_for(p, 0, n, stream, few, err, &code)) { set_error(err); return code; }
   }
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
@@ -740,8 +740,8 @@ xg_status xg_graph_capture_rollout(xg_program* p, int64_t n, int32_t steps, void
     std::string err;
     std::lock_guard<std::mutex> lk(p->mu);
     xg_status code = XG_OK;
-    // no module loads while capturing
-    if (!compile_mode(p, 0, err, &code, pick_few(p, 0, n))) { set_error(err); return code; }
+    bool few;  // no module loads while capturing
+    if (!load_for(p, 0, n, stream, few, err, &code)) { set_error(err); return code; }
   }
   hipStream_t s = (hipStream_t)stream;
   hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);

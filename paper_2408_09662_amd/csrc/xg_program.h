@@ -94,6 +94,11 @@ bool build_code(xg_program* p, int mode, std::string& err, xg_status* code = nul
 // XG_ECOMPILE, XG_EUNSUPPORTED (a kernel that cannot be launched as
 // planned) or XG_EDEVICE
 bool compile_mode(xg_program* p, int mode, std::string& err, xg_status* code = nullptr, bool few = false);
+// build_code of every plan the mode has, and those plans loaded too
+bool build_plans(xg_program* p, int mode, std::string& err, xg_status* code);
+bool load_plans(xg_program* p, int mode, std::string& err, xg_status* code);
+// Loads what n instances of `mode` run on `stream` and says which plan that is
+bool load_for(xg_program* p, int mode, int64_t n, void* stream, bool& few, std::string& err, xg_status* code);
 // Whether n instances of `mode` run the plan for few tiles (formed and
 // planned by this call if need be; the caller holds p->mu)
 bool pick_few(xg_program* p, int mode, int64_t n);

@@ -16,4 +16,23 @@ int probe_batch_source(xg_program** ps, int k, const char* path) {
   return (int)st;
 }
 
+// Whether n instances of `mode` run the plan for few tiles.
+int probe_few(xg_program* p, int mode, long long n) {
+  std::lock_guard<std::mutex> lk(p->mu);
+  return xg::pick_few(p, mode, n);
+}
+
+// Devices that hold the code of a plan of `mode`.
+int probe_loaded(xg_program* p, int mode, int few) { return (int)mode_state(p, mode, few != 0).devs.size(); }
+
+// Whether the code objects of a plan of `mode` are compiled.
+int probe_compiled(xg_program* p, int mode, int few) { return mode_state(p, mode, few != 0).compiled; }
+
+// Gives the plan for few tiles a source that does not compile.
+void probe_spoil_few(xg_program* p, int mode) {
+  std::lock_guard<std::mutex> lk(p->mu);
+  (void)xg::pick_few(p, mode, 1);
+  p->few[mode].srcs.assign(1, "#error planted by a test\n");
+}
+
 }  // extern "C"

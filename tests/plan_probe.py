@@ -31,3 +31,19 @@ def batch_source(programs, path):
     arr = (ctypes.c_void_p * len(programs))(*[p._h.value for p in programs])
     xg._abi.check(lib().probe_batch_source(arr, len(programs), os.fsencode(path)))
     return open(path).read()
+
+
+def few(p, mode, n):
+    return bool(lib().probe_few(p._h, mode, ctypes.c_longlong(n)))
+
+
+def loaded(p, mode, few):
+    return lib().probe_loaded(p._h, mode, int(few))
+
+
+def compiled(p, mode, few):
+    return bool(lib().probe_compiled(p._h, mode, int(few)))
+
+
+def spoil_few(p, mode):
+    lib().probe_spoil_few(p._h, mode)
