@@ -206,7 +206,8 @@ xg_status xg_workspace_bytes(xg_program* p, int64_t n, int32_t mode, size_t* byt
  * count (the plan that fills the chip where only that one is loaded). */
 xg_status xg_compile(xg_program* p, int32_t mode);
 
-/* Generate and compile the code objects of `mode` into the on-disk cache
+/* Generate and compile the code objects of `mode` (both plans' where the
+ * library chose them) into the on-disk cache
  * without touching any device (works on a machine without a GPU).  The
  * cache directory is $XG_CACHE_DIR, else "_kcache" next to the library. */
 xg_status xg_precompile(xg_program* p, int32_t mode);

@@ -809,7 +809,7 @@ xg_status xg_precompile(xg_program* p, int32_t mode) {
   std::lock_guard<std::mutex> lk(p->mu);
   try {
     xg_status code = XG_OK;
-    if (!build_code(p, mode, err, &code)) { set_error(err); return code; }
+    if (!build_plans(p, mode, err, &code)) { set_error(err); return code; }
   } catch (const std::exception& e) { set_error(e.what()); return XG_ENOMEM; }
   return XG_OK;
 }
