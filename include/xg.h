@@ -99,15 +99,16 @@ typedef struct {
 } xg_program_desc;
 
 /* Compilation and launch options.  Zero means "library default".  With every
- * launch option zero (block, ipt, chunk_ops, reg_budget, lds_slots, prefetch,
- * waves, coop_phase) the library plans each mode twice, for launches that
+ * launch option (block, ipt, chunk_ops, reg_budget, lds_slots, prefetch,
+ * waves, coop_phase) zero or at its stated default the library plans each mode twice, for launches that
  * fill the chip and for launches of few 64-instance tiles, and each call runs
  * the plan modelled faster for its n (programs with binary32 tags keep one
  * plan).  A program rounds alike in all of its plans. */
 typedef struct {
   int32_t block;       /* threads per workgroup: 64, 128, 256 (default 64) */
   int32_t ipt;         /* instances per thread: 1, 2, 4 (default 1) */
-  int32_t chunk_ops;   /* max operations per kernel of a chunked program */
+  int32_t chunk_ops;   /* max operations per kernel of a chunked program
+                          (default 20,000) */
   int32_t reg_budget;  /* max live values held in registers before the
                           planner spills to LDS (per instance) */
   int32_t lds_slots;   /* max LDS spill slots per lane */

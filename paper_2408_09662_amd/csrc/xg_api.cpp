@@ -25,7 +25,7 @@ using namespace xg;
 
 namespace xg {
 
-xg_options defaults(const xg_options* o, int dtype, bool mixed) {
+xg_options defaults(const xg_options* o, int dtype, bool library) {
   xg_options d;
   std::memset(&d, 0, sizeof d);
   if (o) d = *o;
@@ -33,18 +33,17 @@ xg_options defaults(const xg_options* o, int dtype, bool mixed) {
   if (d.block <= 0) d.block = 64;
   if (d.ipt <= 0) d.ipt = 1;
   if (d.chunk_ops <= 0) d.chunk_ops = 20000;
-  // A caller that sets no launch option gets one wave per SIMD: all of its
-  // registers, a quarter of the CU's LDS per workgroup (pick_few has the
-  // plan for launches too small for that).  With the whole LDS for one
-  // workgroup three of the four SIMDs idle (the pendulum at 65,536
-  // instances: 151 us, 43 with a quarter and 224 values in registers).
-  const bool alone = !mixed && d.reg_budget <= 0 && d.lds_slots <= 0 && d.waves == 1 && d.block == 64 && d.ipt == 1;
+  // The library's budgets: one wave per SIMD, all of its registers and a
+  // quarter of the CU's LDS per workgroup (pick_few has the plan for launches
+  // too small for that).  With the whole LDS for one workgroup three of the
+  // four SIMDs idle (the pendulum at 65,536 instances: 151 us, 43 with a
+  // quarter and 224 values in registers).
   // 16-wave cooperative tiles put 4 waves on each SIMD: 128 registers each
   if (d.reg_budget <= 0) d.reg_budget = d.waves >= 16 ? (dtype == XG_F32 ? 96 : 48)
-                                        : alone       ? (dtype == XG_F32 ? 333 : 224)
+                                        : library     ? (dtype == XG_F32 ? 333 : 224)
                                                       : (dtype == XG_F32 ? kTuneRegs32 : kTuneRegs64);
   if (d.lds_slots < 0) d.lds_slots = 0;
-  if (alone) d.lds_slots = (int32_t)(kLdsSpillBytes / 4 / ((int64_t)64 * (dtype == XG_F32 ? 4 : 8)));
+  if (library) d.lds_slots = (int32_t)(kLdsSpillBytes / 4 / ((int64_t)64 * (dtype == XG_F32 ? 4 : 8)));
   // the plan allocates only the spill slots it needs, up to all 160 KiB
   if (d.lds_slots == 0)  // all of the 160 KiB but 512 B kept for the kernels' own variables
     d.lds_slots = (int32_t)(kLdsSpillBytes / ((int64_t)d.block * d.ipt * d.waves *
@@ -160,9 +159,9 @@ bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
   // the compiler has to rotate values beyond 128 through accumulation
   // registers, which only pays while it saves spills (a 48 x 48 LDL^T solve,
   // 1,272 live values: 1,020 B of scratch per lane at 224, none at 160)
-  if (p->library_plan[mode] && mode == 0 && p->g.dtype != XG_F32 && M.plan.max_live > budget * 4 / 3)
+  if (mode == 0 && p->library_budget[0] && p->g.dtype != XG_F32 && M.plan.max_live > budget * 4 / 3)
     eo.reg_budget = std::min(budget, 160);
-  if (mode != 0 && p->library_plan[mode]) {
+  if (mode != 0 && p->library_budget[mode]) {
     if (p->g.dtype == XG_F32) eo.reg_budget = kTuneRegs32;
     else eo.reg_budget = !long_adjoint ? kTuneRegs64 : M.plan.max_live > 300 ? 168 : 130;
     // A budget that holds every value leaves a source without reloads, hence
@@ -706,13 +705,19 @@ xg_status xg_program_load(const xg_program_desc* desc, const xg_options* opts, x
   std::string err;
   try {
     if (!build_graph(*desc, p->g, err)) { set_error(err); return XG_EINVAL; }
-    const bool mixed = mixed_precision(p->g);
-    p->opt = defaults(opts, desc->dtype, mixed);
-    const bool lib = !mixed && (!opts || (opts->block <= 0 && opts->ipt <= 0 && opts->chunk_ops <= 0 && opts->reg_budget <= 0 &&
-                               opts->lds_slots <= 0 && opts->prefetch == 0 && opts->waves <= 0 && opts->coop_phase <= 0));
+    // (a caller that writes a default out gets what leaving it out gives)
+    const xg_options none{}, &o = opts ? *opts : none;
+    auto left = [](int32_t v, int32_t d) { return v <= 0 || v == d; };
+    const bool budgets = !mixed_precision(p->g) && o.reg_budget <= 0 && o.lds_slots <= 0 && left(o.block, 64) &&
+                         left(o.ipt, 1) && left(o.waves, 1);
+    const bool lib = budgets && left(o.chunk_ops, 20000) && (o.prefetch == 0 || o.prefetch == 24) && o.coop_phase <= 0;
+    p->opt = defaults(opts, desc->dtype, budgets);
+    const xg_options adj = defaults(opts, desc->dtype, lib);
     for (bool& l : p->library_plan) l = lib;
+    p->library_budget[0] = budgets;
+    p->library_budget[1] = p->library_budget[2] = lib;
     if (!check_opts(p->opt, desc->dtype, err)) { set_error(err); return XG_EINVAL; }
-    p->aopt = p->opt;
+    p->aopt = adj;
     if (p->opt.eager) {
       xg_status code = XG_OK;
       if (!load_plans(p.get(), 0, err, &code)) {

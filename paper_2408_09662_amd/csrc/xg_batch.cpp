@@ -339,7 +339,7 @@ std::vector<xg_options> tune_candidates(xg_program* p, int64_t n, int mode) {
   xg_options base = mode_opt(p, mode);
   const int64_t es = p->g.dtype == XG_F32 ? 4 : 8;
   const int64_t kCUs = 256, kSIMDs = 1024;
-  if (p->library_plan[mode]) {
+  if (p->library_budget[mode]) {
     base.reg_budget = p->g.dtype == XG_F32 ? kTuneRegs32 : kTuneRegs64;
     base.lds_slots = (int32_t)(kLdsSpillBytes / (64 * es));
   }
@@ -880,12 +880,13 @@ xg_status tune_mode(xg_program* p, int64_t n, int mode, size_t workspace_bytes, 
     if (mode == 0) {
       reset_mode(p, 0);
       p->opt = o;
-      p->library_plan[0] = false;
+      p->library_plan[0] = p->library_budget[0] = false;
     } else {
       reset_mode(p, 1);
       reset_mode(p, 2);
       p->aopt = o;
       p->library_plan[1] = p->library_plan[2] = false;
+      p->library_budget[1] = p->library_budget[2] = false;
     }
     return true;
   };

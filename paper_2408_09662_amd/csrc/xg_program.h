@@ -51,7 +51,9 @@ inline size_t ws_bytes_of(int64_t n, int32_t slots, int block, int ipt, size_t e
   return (size_t)tiles * (size_t)slots * (size_t)per * es;
 }
 
-xg_options defaults(const xg_options* o, int dtype, bool mixed);
+// o with the defaults filled in; `library`: the budgets are the library's
+// (library_budget of the mode), else what they are beside other options
+xg_options defaults(const xg_options* o, int dtype, bool library);
 EmitOptions emit_options_of(const xg_options& o);
 bool check_opts(const xg_options& o, int dtype, std::string& err);
 
@@ -67,6 +69,11 @@ struct xg_program {
   // the chip (pick_few).  Both plans of a mode round alike, so which one
   // runs shows in the time only.
   bool library_plan[3] = {false, false, false};
+  // A mode whose register and LDS budgets are the library's: plan_mode may
+  // lower them by what the program's graph holds.  Forward: the caller set
+  // neither them nor the workgroup's shape.  Adjoint: library_plan, as its
+  // budgets were measured with the library's chunks.
+  bool library_budget[3] = {false, false, false};
   int few_state[3] = {0, 0, 0};  // 0 not formed yet, 1 formed, -1 none
   int64_t few_most[3] = {0, 0, 0};  // most instances that run it
   xg_options few_opt[3];
