@@ -11,6 +11,8 @@
 // live; values that cross a cut go to a structure-of-arrays workspace.
 #include <algorithm>
 #include <atomic>
+#include <functional>
+#include <mutex>
 #include <queue>
 #include <stdexcept>
 #include <system_error>
@@ -325,7 +327,17 @@ struct PhasedResult {
   int64_t est = 0;                            // modelled time (cost units)
 };
 
-PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, int64_t cut_max, Policy policy) {
+// The clusters of one duplication threshold and subtree cap.
+struct Clusters {
+  std::vector<std::vector<int32_t>> members;    // by root: its nodes, in order
+  std::vector<int64_t> cost;                    // by root
+  std::vector<std::vector<int32_t>> eff, cone;  // by root: see below
+  std::vector<std::vector<int32_t>> users, dup_users;  // the same relations from the other end
+  std::vector<int32_t> scheduled;               // exchanged clusters
+  std::vector<int64_t> path;                    // longest remaining path
+};
+
+Clusters clusters_of(const Graph& g, int64_t dup_max, int64_t cut_max) {
   const int32_t n = (int32_t)g.nodes.size();
   auto sched = [&](int32_t v) {
     const int op = g.nodes[v].op;
@@ -407,11 +419,12 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
     cone[r].swap(d);
   }
   std::vector<int32_t> sc;  // scheduled (exchanged) clusters
-  std::vector<std::vector<int32_t>> esucc(n);
+  std::vector<std::vector<int32_t>> esucc(n), dsucc(n);
   for (int32_t r : clusters)
     if (!dup[r]) {
       sc.push_back(r);
       for (int32_t p : eff[r]) esucc[p].push_back(r);
+      for (int32_t d : cone[r]) dsucc[d].push_back(r);
     }
   std::vector<int64_t> bl(n, 0);
   for (auto it = sc.rbegin(); it != sc.rend(); ++it) {
@@ -419,22 +432,41 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
     for (int32_t s : esucc[*it]) m = std::max(m, bl[s]);
     bl[*it] = ccost[*it] + m;
   }
+  Clusters C;
+  C.members.swap(members);
+  C.cost.swap(ccost);
+  C.eff.swap(eff);
+  C.cone.swap(cone);
+  C.users.swap(esucc);
+  C.dup_users.swap(dsucc);
+  C.scheduled.swap(sc);
+  C.path.swap(bl);
+  return C;
+}
+
+// at[v]: the place of node v in the low-pressure order (cost units before and
+// with it).
+PhasedResult phased_schedule(const Graph& g, const Clusters& C, const std::vector<int64_t>& at, int W, int64_t T,
+                             Policy policy) {
+  const int32_t n = (int32_t)g.nodes.size();
+  const auto &members = C.members, &eff = C.eff, &cone = C.cone, &esucc = C.users;
+  const auto& ccost = C.cost;
+  const auto& sc = C.scheduled;
   // Ready clusters of a wave, and which exchanged values it holds (computed
   // or received).  A wave takes the ready cluster with the largest score:
   // the rank its policy gives (the longest remaining path, or the place in
   // the low-pressure order), less what taking it here would add in loads of
   // values the wave does not hold, stores of values nobody exported yet and
-  // duplicated operands.
-  std::vector<int64_t> rank(n, 0);
-  if (policy.by_order) {
-    std::vector<int64_t> at(n, 0);
-    int64_t t = 0;
-    for (int32_t v : low_pressure_order(g)) { t += op_cost(g.nodes[v].op); at[v] = t; }
-    for (int32_t r : sc) rank[r] = -at[r] / W;
-  } else {
-    for (int32_t r : sc) rank[r] = bl[r];
-  }
-  std::vector<std::vector<int32_t>> ready(W);
+  // duplicated operands (the first of equal ones).  A score only ever rises
+  // (as values arrive), so each wave's heap gets an entry per change and the
+  // entries that are out of date are skipped: a wide program has thousands of
+  // clusters ready at once (a 30,000-operation DAG on 64 inputs plans in 2 s,
+  // 30 when every choice looked at all of them).
+  auto rank = [&](int32_t r) { return policy.by_order ? -at[r] / W : C.path[r]; };
+  typedef std::pair<int64_t, int32_t> Entry;  // score, -cluster: the largest is taken
+  std::vector<std::priority_queue<Entry>> ready(W);
+  std::vector<std::vector<int64_t>> score(W, std::vector<int64_t>(n, 0));
+  std::vector<std::vector<char>> queued(W, std::vector<char>(n, 0));
   std::vector<std::vector<int32_t>> miss(W, std::vector<int32_t>(n, 0));
   std::vector<std::vector<char>> have(W, std::vector<char>(n, 0));  // duplicated clusters on each wave
   std::vector<std::vector<char>> held(W, std::vector<char>(n, 0));  // exchanged values on each wave
@@ -442,14 +474,40 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
   for (int w = 0; w < W; ++w)
     for (int32_t r : sc) {
       miss[w][r] = (int32_t)eff[r].size();
-      if (miss[w][r] == 0) ready[w].push_back(r);
     }
+  // what cluster c would add in transfers on wave w
+  auto comm_of = [&](int w, int32_t c) {
+    int64_t x = 0;
+    for (int32_t p : eff[c])
+      if (!held[w][p]) x += kLoadCost + (exported[p] ? 0 : kStoreCost);
+    return x;
+  };
+  auto enqueue = [&](int w, int32_t c) {
+    int64_t s = rank(c);
+    if (policy.weight) {
+      int64_t y = 0;
+      for (int32_t d : cone[c])
+        if (!have[w][d]) y += ccost[d];
+      s -= policy.weight * (comm_of(w, c) + y);
+    }
+    score[w][c] = s;
+    queued[w][c] = 1;
+    ready[w].push({s, -c});
+  };
   PhasedResult res;
   res.lists.assign(W, {});
   res.phases.assign(W, {});
   res.node_phase.assign(n, -1);
   res.owner.assign(n, -1);
   std::vector<char> done(n, 0);
+  auto rise = [&](int w, const std::vector<int32_t>& users, int64_t by) {
+    if (!policy.weight) return;
+    for (int32_t c : users)
+      if (queued[w][c] && !done[c]) ready[w].push({score[w][c] += policy.weight * by, -c});
+  };
+  for (int w = 0; w < W; ++w)
+    for (int32_t r : sc)
+      if (miss[w][r] == 0) enqueue(w, r);
   size_t remaining = sc.size();
   int32_t phase = 0;
   std::vector<std::vector<int64_t>> loads;
@@ -470,37 +528,32 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
       int64_t target = T;
       for (int x = 0; x < W; ++x) target = std::max(target, load[x]);
       if (starved) target = std::max<int64_t>(40, T / 4);
-      int32_t r = -1;
-      int64_t best = 0, comm = 0;
-      size_t keep = 0;
       auto& q = ready[w];
-      for (size_t i = 0; i < q.size(); ++i) {
-        const int32_t c = q[i];
-        if (done[c]) continue;
-        q[keep++] = c;
-        int64_t x = 0;
-        for (int32_t p : eff[c])
-          if (!held[w][p]) x += kLoadCost + (exported[p] ? 0 : kStoreCost);
-        int64_t y = 0;
-        for (int32_t d : cone[c])
-          if (!have[w][d]) y += ccost[d];
-        const int64_t sco = rank[c] - policy.weight * (x + y);
-        if (r < 0 || sco > best || (sco == best && c < r)) { r = c; best = sco; comm = x; }
-      }
-      q.resize(keep);
+      while (!q.empty() && (done[-q.top().second] || q.top().first != score[w][-q.top().second])) q.pop();
+      const int32_t r = q.empty() ? -1 : -q.top().second;
       if (r < 0 || load[w] >= target) {
         if (r < 0) starved = true;
         active[w] = 0;
         --n_active;
         continue;
       }
+      q.pop();
       done[r] = 1;
       --remaining;
-      for (int32_t p : eff[r])
-        if (!held[w][p]) { held[w][p] = 1; exported[p] = 1; }
+      const int64_t comm = comm_of(w, r);
+      for (int32_t p : eff[r]) {
+        if (held[w][p]) continue;
+        rise(w, esucc[p], kLoadCost + (exported[p] ? 0 : kStoreCost));
+        held[w][p] = 1;
+        if (exported[p]) continue;
+        exported[p] = 1;
+        for (int x = 0; x < W; ++x)
+          if (!held[x][p]) rise(x, esucc[p], kStoreCost);
+      }
       for (int32_t d : cone[r]) {
         if (have[w][d]) continue;
         have[w][d] = 1;
+        rise(w, C.dup_users[d], ccost[d]);
         load[w] += ccost[d];
         for (int32_t v : members[d]) { res.lists[w].push_back(v); res.phases[w].push_back(phase); }
       }
@@ -514,14 +567,14 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
       held[w][r] = 1;
       newly.push_back({w, r});
       for (int32_t s : esucc[r])
-        if (--miss[w][s] == 0 && !done[s]) ready[w].push_back(s);
+        if (--miss[w][s] == 0 && !done[s]) enqueue(w, s);
     }
     if (newly.empty()) throw std::logic_error("phased plan: no cluster became ready");
     for (auto& wr : newly)
       for (int x = 0; x < W; ++x) {
         if (x == wr.first) continue;
         for (int32_t s : esucc[wr.second])
-          if (--miss[x][s] == 0 && !done[s]) ready[x].push_back(s);
+          if (--miss[x][s] == 0 && !done[s]) enqueue(x, s);
       }
     loads.push_back(load);
     ++phase;
@@ -543,12 +596,13 @@ PhasedResult phased_schedule(const Graph& g, int W, int64_t T, int64_t dup_max, 
 
 }  // namespace
 
-// The phased plan of one setting: phases of at least T, duplication threshold
-// D, subtree cap S.
-static Plan phased_plan_of(const Graph& g, const PlanOptions& po, int64_t T, int64_t D, int64_t S, Policy policy) {
+// The phased plan of one setting: clusters of one duplication threshold and
+// subtree cap, phases of at least T.
+static Plan phased_plan_of(const Graph& g, const PlanOptions& po, const Clusters& C, const std::vector<int64_t>& at,
+                           int64_t T, Policy policy) {
   const int32_t n = (int32_t)g.nodes.size();
   const int W = po.waves;
-  PhasedResult r = phased_schedule(g, W, T, D, S, policy);
+  PhasedResult r = phased_schedule(g, C, at, W, T, policy);
   Plan pl;
   pl.waves = W;
   pl.phased = true;
@@ -703,43 +757,62 @@ static Plan phased_plan_of(const Graph& g, const PlanOptions& po, int64_t T, int
 static Plan make_phased_plan(const Graph& g, const PlanOptions& po) {
   std::vector<int64_t> Ts = {std::max(1, po.coop_phase)};
   if (po.coop_phase == kAutoPhase) Ts = {60, 120, 240, 400};
-  struct Setting { int64_t T, D, S; Policy p; };
-  std::vector<Setting> st;
   // (a weight of 1,000 ranks by transfers alone: fewer values are held by two
   // waves, for programs that spill much)
   std::vector<Policy> policies = {Policy{false, 0}, Policy{false, 2}, Policy{true, 1}, Policy{true, 2}, Policy{true, 4}};
   if (po.transfers_first) policies = {Policy{false, 1000}};
+  std::vector<std::pair<int64_t, int64_t>> shapes;  // duplication threshold, subtree cap
+  for (int64_t D : {1, 3})
+    for (int64_t S : {8, 16, 24, 48}) shapes.push_back({D, S});
+  struct Setting { int64_t T; size_t shape; Policy p; };
+  std::vector<Setting> st;
   for (Policy p : policies)
     for (int64_t T : Ts)
-      for (int64_t D : {1, 3})
-        for (int64_t S : {8, 16, 24, 48}) st.push_back({T, D, S, p});
-  std::vector<Plan> pls(st.size());
-  std::vector<std::string> errs(st.size());
-  std::atomic<size_t> next{0};
-  auto work = [&]() {
-    for (size_t i; (i = next++) < st.size();) {
-      try {
-        pls[i] = phased_plan_of(g, po, st[i].T, st[i].D, st[i].S, st[i].p);
-      } catch (const std::exception& e) {
-        errs[i] = e.what();
-      }
+      for (size_t k = 0; k < shapes.size(); ++k) st.push_back({T, k, p});
+  std::vector<int64_t> at(g.nodes.size(), 0);
+  int64_t place = 0;
+  for (int32_t v : low_pressure_order(g)) at[v] = place += op_cost(g.nodes[v].op);
+  // f(0) ... f(n - 1) on several threads
+  auto each = [](size_t n, const std::function<void(size_t)>& f) {
+    std::atomic<size_t> next{0};
+    auto work = [&]() { for (size_t i; (i = next++) < n;) f(i); };
+    std::vector<std::thread> th;
+    th.reserve(8);
+    const unsigned hw = std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
+    try {
+      for (unsigned k = 1; k < hw && k < n; ++k) th.emplace_back(work);
+    } catch (const std::system_error&) {
+      // fewer threads: this one does what they do not
+    }
+    work();
+    for (auto& t : th) t.join();
+  };
+  std::vector<Clusters> cl(shapes.size());
+  std::string err;
+  std::mutex mu;
+  Plan best;
+  size_t best_i = st.size();
+  auto guarded = [&](const std::function<void()>& f) {  // (nothing leaves a thread)
+    try {
+      f();
+    } catch (const std::exception& e) {
+      std::lock_guard<std::mutex> lk(mu);
+      if (err.empty()) err = e.what();
     }
   };
-  std::vector<std::thread> th;
-  th.reserve(8);
-  const unsigned hw = std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
-  try {
-    for (unsigned k = 1; k < hw; ++k) th.emplace_back(work);
-  } catch (const std::system_error&) {
-    // fewer threads: this one plans what they do not
-  }
-  work();
-  for (auto& t : th) t.join();
-  size_t best = st.size();
-  for (size_t i = 0; i < st.size(); ++i)
-    if (errs[i].empty() && (best == st.size() || pls[i].coop_est < pls[best].coop_est)) best = i;
-  if (best == st.size()) throw std::logic_error(errs[0]);
-  return std::move(pls[best]);
+  each(shapes.size(), [&](size_t k) { guarded([&]() { cl[k] = clusters_of(g, shapes[k].first, shapes[k].second); }); });
+  if (!err.empty()) throw std::logic_error(err);
+  each(st.size(), [&](size_t i) {
+    guarded([&]() {
+      Plan pl = phased_plan_of(g, po, cl[st[i].shape], at, st[i].T, st[i].p);
+      std::lock_guard<std::mutex> lk(mu);
+      if (best_i < st.size() && (pl.coop_est > best.coop_est || (pl.coop_est == best.coop_est && i > best_i))) return;
+      best = std::move(pl);
+      best_i = i;
+    });
+  });
+  if (best_i == st.size()) throw std::logic_error(err);
+  return best;
 }
 
 Plan make_plan(const Graph& g, const PlanOptions& po) {

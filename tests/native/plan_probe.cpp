@@ -28,6 +28,18 @@ int probe_loaded(xg_program* p, int mode, int few) { return (int)mode_state(p, m
 // Whether the code objects of a plan of `mode` are compiled.
 int probe_compiled(xg_program* p, int mode, int few) { return mode_state(p, mode, few != 0).compiled; }
 
+// A hash of the sources of the plan that n instances of `mode` run, and its phases.
+unsigned long long probe_code(xg_program* p, int mode, long long n, int* phases) {
+  std::lock_guard<std::mutex> lk(p->mu);
+  std::string err;
+  if (!xg::plan_mode(p, mode, err)) return 0;
+  const xg::ModeState& M = mode_state(p, mode, xg::pick_few(p, mode, n));
+  *phases = M.plan.n_phases;
+  uint64_t h = 1469598103934665603ull;
+  for (const std::string& s : M.srcs) h = xg::fnv1a(s, h);
+  return h;
+}
+
 // Gives the plan for few tiles a source that does not compile.
 void probe_spoil_few(xg_program* p, int mode) {
   std::lock_guard<std::mutex> lk(p->mu);

@@ -47,3 +47,11 @@ def compiled(p, mode, few):
 
 def spoil_few(p, mode):
     lib().probe_spoil_few(p._h, mode)
+
+
+def code(p, mode, n):
+    """(hash of the sources, phases) of the plan that n instances run."""
+    f = lib().probe_code
+    f.restype = ctypes.c_ulonglong
+    phases = ctypes.c_int()
+    return f(p._h, mode, ctypes.c_longlong(n), ctypes.byref(phases)), phases.value
