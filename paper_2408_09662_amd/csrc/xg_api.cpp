@@ -129,7 +129,7 @@ bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
   // there with 130; 6 links (266 live) 89 / 190, 97 / 180 with 168 and
   // 84 / 129 with 130 in kernels of 40,000; 5 links 51 / 92 and 70 / 155 with
   // 168, 4 links 34 / 71 and 41 / 113 in one kernel.
-  const bool long_adjoint = mode != 0 && p->library_plan[mode] && M.n_ops > 2 * (int64_t)opt.chunk_ops;
+  const bool long_adjoint = mode != 0 && p->library_budget[mode] && M.n_ops > 2 * (int64_t)opt.chunk_ops;
   PlanOptions po;
   po.chunk_ops = long_adjoint ? 2 * opt.chunk_ops : opt.chunk_ops;
   po.waves = mode == 0 ? opt.waves : 1;
@@ -146,7 +146,7 @@ bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
   const int64_t half_slots = 160 * 1024 / 2 / (64 * (M.g.dtype == XG_F32 ? 4 : 8));
   if (spill_slots < half_slots) po.xch_cap = std::max<int64_t>(16, half_slots - spill_slots);
   po.reg_budget = opt.reg_budget;
-  po.transfers_first = M.transfers_first;
+  po.transfers_first = mode == 0 && (few ? p->few_transfers_first : p->transfers_first);
   try {
     M.plan = make_plan(M.g, po);
   } catch (const std::logic_error& e) {
@@ -248,6 +248,7 @@ static void form_few(xg_program* p, int mode) {
   if (B.n_ops < 100 || B.n_ops > 60000) return;
   ModeState best;
   xg_options best_o = o;
+  bool best_first = false;
   // A plan's spills add to its modelled time, workspace accesses most of all:
   // an LDL^T solve of 48 x 48 at 10,000 instances takes 247 us with 32,600 +
   // 16,195 accesses on 4 waves, 171 with 35,500 + 8,451; the MPC on 2 waves
@@ -261,13 +262,14 @@ static void form_few(xg_program* p, int mode) {
     o.coop_phase = phase;
     o.lds_slots = (int32_t)(kLdsSpillBytes / (64 * W * es));
     p->few[0] = ModeState();
-    p->few[0].transfers_first = transfers_first;
+    p->few_transfers_first = transfers_first;
     p->few_opt[0] = o;
     if (!plan_mode(p, 0, err, true)) return;
     if (!best.planned || score(p->few[0]) < score(best)) {
       best = std::move(p->few[0]);
       best_o = o;
       best_o.coop_phase = best.plan.phase_len;
+      best_first = transfers_first;
     }
   };
   for (int W : {4, 2}) consider(W, kAutoPhase, false);
@@ -280,6 +282,7 @@ static void form_few(xg_program* p, int mode) {
   p->few[0] = std::move(best);
   if (!p->few[0].planned) return;
   p->few_opt[0] = best_o;
+  p->few_transfers_first = best_first;
   p->few_state[0] = 1;
   int64_t most = kFewTiles;
   while (most > 0 && !few_faster(p, 0, most)) --most;

@@ -292,7 +292,7 @@ xg_status batch_launch(xg_batch* b, const xg_batch_args* args, void* ws, void* s
 // ------------------------------------------------------------ autotune
 // Planner/emitter generation: part of every tuning-cache key, so decisions
 // timed on code an earlier generator emitted are not reused.
-constexpr uint64_t kTuneVersion = 5;
+constexpr uint64_t kTuneVersion = 6;
 
 // Key of a program for the tuning caches: its graph (per-instruction
 // binary32 tags included: a mixed-precision program is timed on its own
@@ -335,7 +335,7 @@ std::string tune_path(const xg_program* p, int64_t n, int mode) {
 // leaf lengths and fan-outs at three register budgets; for the forward,
 // cooperative tiles (level-split for wide programs with few tiles, phased
 // for narrow ones, 2-wave phased also at one tile per SIMD or more).
-std::vector<xg_options> tune_candidates(xg_program* p, int64_t n, int mode) {
+std::vector<Candidate> tune_candidates(xg_program* p, int64_t n, int mode) {
   xg_options base = mode_opt(p, mode);
   const int64_t es = p->g.dtype == XG_F32 ? 4 : 8;
   const int64_t kCUs = 256, kSIMDs = 1024;
@@ -356,13 +356,13 @@ std::vector<xg_options> tune_candidates(xg_program* p, int64_t n, int mode) {
   std::vector<int64_t> ldss = {full};
   const int64_t fit = lds_fit(base.block, base.ipt);
   if (fit < full) ldss.push_back(fit);
-  std::vector<xg_options> cands;
+  std::vector<Candidate> cands;
   const int rb0 = base.reg_budget;
-  {  // what runs untuned (forward; the adjoint's candidates keep smaller workspaces)
+  {  // what runs untuned, exactly: tuning never ends on a slower plan
     std::lock_guard<std::mutex> lk(p->mu);
-    if (mode == 0 && p->library_plan[0]) {
-      cands.push_back(mode_opt(p, mode));
-      if (pick_few(p, mode, n)) cands.push_back(mode_opt(p, mode, true));
+    if (p->library_budget[mode]) {
+      cands.emplace_back(mode_opt(p, mode), true);
+      if (pick_few(p, mode, n)) cands.emplace_back(mode_opt(p, mode, true), true, mode == 0 && p->few_transfers_first);
     }
   }
   for (int64_t l : ldss)
@@ -574,15 +574,51 @@ void reset_modes(xg_program* p) {
   for (int m = 0; m < 3; ++m) reset_mode(p, m);
 }
 
-// A copy of p (graph and options) whose `mode` options are o.
-std::unique_ptr<xg_program> trial_program(const xg_program* p, int mode, const xg_options& o) {
+// Makes c the plan of p's `mode` (1 and 2 share one), for every count.
+void adopt(xg_program* p, int mode, const Candidate& c) {
+  if (mode == 0) {
+    p->opt = c.o;
+    p->transfers_first = c.transfers_first;
+    p->library_plan[0] = false;
+    p->library_budget[0] = c.library;
+  } else {
+    p->aopt = c.o;
+    p->library_plan[1] = p->library_plan[2] = false;
+    p->library_budget[1] = p->library_budget[2] = c.library;
+  }
+}
+
+// A copy of p (graph and options) whose `mode` plan is c.
+std::unique_ptr<xg_program> trial_program(const xg_program* p, int mode, const Candidate& c) {
   std::unique_ptr<xg_program> q(new xg_program());
   q->g = p->g;
   q->opt = p->opt;
   q->aopt = p->aopt;
-  (mode == 0 ? q->opt : q->aopt) = o;
+  adopt(q.get(), mode, c);
   return q;
 }
+
+}  // namespace
+
+namespace xg {
+bool plan_candidates(xg_program* p, int64_t n, int mode, std::vector<Candidate>& cands,
+                     std::vector<std::unique_ptr<xg_program>>& trials, std::string& err) {
+  for (const Candidate& c : tune_candidates(p, n, mode)) {
+    std::unique_ptr<xg_program> q = trial_program(p, mode, c);
+    if (!plan_mode(q.get(), mode, err)) {
+      if (c.o.waves <= 1) return false;
+      // a cooperative plan that cannot be formed (e.g. LDS): not a candidate
+      if (c.o.verbose) std::fprintf(stderr, "[xg autotune] cooperative candidate skipped: %s\n", err.c_str());
+      continue;
+    }
+    cands.push_back(c);
+    trials.push_back(std::move(q));
+  }
+  return true;
+}
+}  // namespace xg
+
+namespace {
 
 }  // namespace
 
@@ -807,17 +843,13 @@ xg_status xg_autotune_workspace_bytes(xg_program* p, int64_t n, int32_t mode, si
   if (!p || n <= 0 || !bytes || mode < 0 || mode > 2) { set_error("bad argument"); return XG_EINVAL; }
   std::string err;
   try {
+    std::vector<Candidate> cands;
+    std::vector<std::unique_ptr<xg_program>> trials;
+    if (!plan_candidates(p, n, mode, cands, trials, err)) { set_error(err); return XG_EINVAL; }
     size_t mx = 0;
-    for (auto& o : tune_candidates(p, n, mode)) {
-      std::unique_ptr<xg_program> q = trial_program(p, mode, o);
-      if (!plan_mode(q.get(), mode, err)) {
-        if (o.waves > 1) continue;  // a cooperative plan that cannot be formed: not a candidate
-        set_error(err);
-        return XG_EINVAL;
-      }
-      mx = std::max(mx, ws_bytes_of(n, q->m[mode].ws_slots(), o.block, o.ipt,
+    for (size_t i = 0; i < cands.size(); ++i)
+      mx = std::max(mx, ws_bytes_of(n, trials[i]->m[mode].ws_slots(), cands[i].o.block, cands[i].o.ipt,
                                     p->g.dtype == XG_F32 ? 4 : 8));
-    }
     *bytes = mx;
   } catch (const std::exception& e) {
     set_error(e.what());
@@ -830,16 +862,12 @@ xg_status xg_autotune_precompile(xg_program* p, int64_t n, int32_t mode) {
   if (!p || n <= 0 || mode < 0 || mode > 2) { set_error("bad argument"); return XG_EINVAL; }
   std::string err;
   try {
+    std::vector<Candidate> cands;
+    std::vector<std::unique_ptr<xg_program>> trials;
+    if (!plan_candidates(p, n, mode, cands, trials, err)) { set_error(err); return XG_EINVAL; }
     std::vector<std::string> srcs;
-    for (auto& o : tune_candidates(p, n, mode)) {
-      std::unique_ptr<xg_program> q = trial_program(p, mode, o);
-      if (!plan_mode(q.get(), mode, err)) {
-        if (o.waves > 1) continue;  // a cooperative plan that cannot be formed: not a candidate
-        set_error(err);
-        return XG_EINVAL;
-      }
+    for (auto& q : trials)
       for (auto& s : q->m[mode].srcs) srcs.push_back(s);
-    }
     std::vector<CodeObject> cos;
     if (!compile_many(srcs, base_compile_options(p->opt.strict != 0), cos, err, p->opt.verbose != 0)) {
       set_error(err);
@@ -874,20 +902,12 @@ xg_status tune_mode(xg_program* p, int64_t n, int mode, size_t workspace_bytes, 
   }
   const std::string path = tune_path(p, n, mode);
   const xg_options base = mode_opt(p, mode);
-  auto apply = [&](const xg_options& o) {
+  auto apply = [&](const Candidate& c) {
     std::lock_guard<std::mutex> lk(p->mu);
     if (p->live_graphs > 0) return false;  // captured meanwhile on another thread
-    if (mode == 0) {
-      reset_mode(p, 0);
-      p->opt = o;
-      p->library_plan[0] = p->library_budget[0] = false;
-    } else {
-      reset_mode(p, 1);
-      reset_mode(p, 2);
-      p->aopt = o;
-      p->library_plan[1] = p->library_plan[2] = false;
-      p->library_budget[1] = p->library_budget[2] = false;
-    }
+    for (int m = 0; m < 3; ++m)
+      if ((m == 0) == (mode == 0)) reset_mode(p, m);
+    adopt(p, mode, c);
     return true;
   };
   auto refused = [&]() {
@@ -899,42 +919,31 @@ xg_status tune_mode(xg_program* p, int64_t n, int mode, size_t workspace_bytes, 
     std::ifstream f(path);
     xg_options o = base;
     if (f >> o.block >> o.ipt >> o.reg_budget >> o.lds_slots >> o.prefetch >> o.chunk_ops >> o.waves) {
-      int32_t sg = 0, fo = 0, cp = 0;
+      int32_t sg = 0, fo = 0, cp = 0, lib = 0, first = 0;
       if (f >> sg && sg > 0) o.adj_seg_ops = sg;
       if (f >> fo && fo > 0) o.adj_fanout = fo;
       if (f >> cp && cp >= 0) o.coop_phase = cp;
+      f >> lib >> first;
       std::string err;
       if (check_opts(o, p->g.dtype, err)) {
-        if (!apply(o)) return refused();
+        if (!apply(Candidate(o, lib == 1, first == 1))) return refused();
         if (chosen) *chosen = o;
         return XG_OK;
       }
     }
   }
-  std::vector<xg_options> cands = tune_candidates(p, n, mode);
+  std::vector<Candidate> cands;
   // plan all candidates, then compile every source concurrently
   std::vector<std::unique_ptr<xg_program>> trial;
   std::vector<std::string> srcs;
   std::vector<size_t> first;
   std::string err;
   try {
-    std::vector<xg_options> planned;
-    for (auto& o : cands) {
-      std::unique_ptr<xg_program> q = trial_program(p, mode, o);
-      if (!plan_mode(q.get(), mode, err)) {
-        if (o.waves > 1) {  // a cooperative plan that cannot be formed (e.g. LDS): not a candidate
-          if (base.verbose) std::fprintf(stderr, "[xg autotune] cooperative candidate skipped: %s\n", err.c_str());
-          continue;
-        }
-        set_error(err);
-        return XG_EINVAL;
-      }
-      planned.push_back(o);
+    if (!plan_candidates(p, n, mode, cands, trial, err)) { set_error(err); return XG_EINVAL; }
+    for (auto& q : trial) {
       first.push_back(srcs.size());
       for (auto& s : q->m[mode].srcs) srcs.push_back(s);
-      trial.push_back(std::move(q));
     }
-    cands.swap(planned);
     std::vector<CodeObject> cos;
     if (!compile_many(srcs, base_compile_options(base.strict != 0), cos, err, base.verbose != 0)) {
       set_error(err);
@@ -979,10 +988,11 @@ xg_status tune_mode(xg_program* p, int64_t n, int mode, size_t workspace_bytes, 
     }
     t[i] = time_one(i);
     if (base.verbose && t[i] >= 0)
-      std::fprintf(stderr, "[xg autotune] mode %d n=%lld block=%d ipt=%d reg=%d lds=%d prefetch=%d chunk=%d waves=%d phase=%d seg=%d fanout=%d: %.2f us\n",
-                   mode, (long long)n, cands[i].block, cands[i].ipt, cands[i].reg_budget, cands[i].lds_slots,
-                   cands[i].prefetch, cands[i].chunk_ops, cands[i].waves, cands[i].coop_phase, cands[i].adj_seg_ops,
-                   cands[i].adj_fanout, 1e3 * t[i] / reps);
+      std::fprintf(stderr, "[xg autotune] mode %d n=%lld block=%d ipt=%d reg=%d lds=%d prefetch=%d chunk=%d waves=%d phase=%d seg=%d fanout=%d%s%s: %.2f us\n",
+                   mode, (long long)n, cands[i].o.block, cands[i].o.ipt, cands[i].o.reg_budget, cands[i].o.lds_slots,
+                   cands[i].o.prefetch, cands[i].o.chunk_ops, cands[i].o.waves, cands[i].o.coop_phase,
+                   cands[i].o.adj_seg_ops, cands[i].o.adj_fanout, cands[i].library ? " library" : "",
+                   cands[i].transfers_first ? " transfers" : "", 1e3 * t[i] / reps);
   }
   // the three fastest are timed twice more, in turn, and each keeps its
   // best time: one pass in sequence can catch a candidate in a slow moment
@@ -1009,13 +1019,13 @@ xg_status tune_mode(xg_program* p, int64_t n, int mode, size_t workspace_bytes, 
   (void)hipEventDestroy(e1);
   for (auto& q : trial) reset_modes(q.get());
   if (besti < 0) { set_error("autotune: no candidate fits the workspace"); return XG_ENOMEM; }
-  const xg_options& o = cands[besti];
-  if (!apply(o)) return refused();
+  const xg_options& o = cands[besti].o;
+  if (!apply(cands[besti])) return refused();
   {
     std::ofstream f(path);
     f << o.block << " " << o.ipt << " " << o.reg_budget << " " << o.lds_slots << " " << o.prefetch
       << " " << o.chunk_ops << " " << o.waves << " " << o.adj_seg_ops << " " << o.adj_fanout << " "
-      << o.coop_phase << "\n";
+      << o.coop_phase << " " << cands[besti].library << " " << cands[besti].transfers_first << "\n";
   }
   if (chosen) *chosen = o;
   return XG_OK;

@@ -1,6 +1,7 @@
 // Program object shared by the C-ABI implementation files.
 #pragma once
 
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -29,7 +30,6 @@ struct ModeState {
   Plan plan;
   EmitStats est;
   int64_t recompute_ops = 0;
-  bool transfers_first = false;  // phased plan ranked by transfers (form_few)
   int64_t cost = 0;     // modelled time of a tile (units of one vector operation)
   int64_t n_nodes = 0, n_ops = 0;  // SSA values and operations before products join sums
   EmitOptions eo;       // what the sources were emitted with (est counts that emission)
@@ -74,6 +74,8 @@ struct xg_program {
   // neither them nor the workgroup's shape.  Adjoint: library_plan, as its
   // budgets were measured with the library's chunks.
   bool library_budget[3] = {false, false, false};
+  // Forward phased plans ranked by transfers (form_few chose so, or tuning did)
+  bool transfers_first = false, few_transfers_first = false;
   int few_state[3] = {0, 0, 0};  // 0 not formed yet, 1 formed, -1 none
   int64_t few_most[3] = {0, 0, 0};  // most instances that run it
   xg_options few_opt[3];
@@ -112,6 +114,18 @@ bool pick_few(xg_program* p, int mode, int64_t n);
 // Launch options of the library's own plans, before any rule on n: the
 // values xg_autotune's candidates are spread around
 constexpr int kTuneRegs64 = 112, kTuneRegs32 = 200;
+// A plan that tuning may give a mode.
+struct Candidate {
+  xg_options o;
+  // what options do not say of a plan: the library's rules lower its budgets,
+  // its phases are ranked by transfers
+  bool library = false, transfers_first = false;
+  Candidate(const xg_options& o_, bool l = false, bool t = false) : o(o_), library(l), transfers_first(t) {}
+};
+// The candidates for n instances of `mode` (cooperative plans that cannot be
+// formed left out) and, for each, a copy of p planned with it
+bool plan_candidates(xg_program* p, int64_t n, int mode, std::vector<Candidate>& cands,
+                     std::vector<std::unique_ptr<xg_program>>& trials, std::string& err);
 // The source of the persistent kernel over progs (host only: nothing is compiled)
 xg_status batch_source(const std::vector<xg_program*>& progs, std::string& src);
 void reset_mode(xg_program* p, int mode);  // drain, unload, forget the plan

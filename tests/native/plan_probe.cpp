@@ -40,6 +40,21 @@ unsigned long long probe_code(xg_program* p, int mode, long long n, int* phases)
   return h;
 }
 
+// Sources (hashes) of the tuning candidates of `mode` for n instances, and
+// whether each is one of the library's plans.  Returns their number.
+int probe_candidates(xg_program* p, int mode, long long n, unsigned long long* hash, int* library, int most) {
+  std::vector<xg::Candidate> cands;
+  std::vector<std::unique_ptr<xg_program>> trials;
+  std::string err;
+  if (!xg::plan_candidates(p, n, mode, cands, trials, err)) return -1;
+  for (size_t i = 0; i < cands.size() && (int)i < most; ++i) {
+    library[i] = cands[i].library;
+    hash[i] = 1469598103934665603ull;
+    for (const std::string& s : trials[i]->m[mode].srcs) hash[i] = xg::fnv1a(s, hash[i]);
+  }
+  return (int)cands.size();
+}
+
 // Gives the plan for few tiles a source that does not compile.
 void probe_spoil_few(xg_program* p, int mode) {
   std::lock_guard<std::mutex> lk(p->mu);

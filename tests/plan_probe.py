@@ -55,3 +55,11 @@ def code(p, mode, n):
     f.restype = ctypes.c_ulonglong
     phases = ctypes.c_int()
     return f(p._h, mode, ctypes.c_longlong(n), ctypes.byref(phases)), phases.value
+
+
+def candidates(p, mode, n):
+    """[(hash of the sources, whether it is the library's)] of the tuning candidates."""
+    h, l = (ctypes.c_ulonglong * 100)(), (ctypes.c_int * 100)()
+    k = lib().probe_candidates(p._h, mode, ctypes.c_longlong(n), h, l, 100)
+    assert 0 < k <= 100
+    return [(h[i], bool(l[i])) for i in range(k)]
