@@ -145,6 +145,7 @@ bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
   const int64_t spill_slots = (int64_t)opt.lds_slots * std::max(1, opt.waves);
   const int64_t half_slots = 160 * 1024 / 2 / (64 * (M.g.dtype == XG_F32 ? 4 : 8));
   if (spill_slots < half_slots) po.xch_cap = std::max<int64_t>(16, half_slots - spill_slots);
+  if (mixed_precision(M.g)) po.xch_cap = po.lds_slots / 2;  // (as make_phased_plan keeps them)
   po.reg_budget = opt.reg_budget;
   po.transfers_first = mode == 0 && (few ? p->few_transfers_first : p->transfers_first);
   try {

@@ -316,6 +316,9 @@ constexpr int64_t kSpillCost = 4;
 struct Policy {
   bool by_order;   // rank by place in the low-pressure order (else longest path)
   int64_t weight;  // of what a choice adds in loads, stores and duplication
+  // programs with binary32 tags: rank by the operands the wave computed
+  // itself, then by path; transfers are not part of a wave's load
+  bool local = false;
 };
 
 struct PhasedResult {
@@ -325,6 +328,7 @@ struct PhasedResult {
   std::vector<int32_t> owner;                 // non-duplicated nodes: their wave (-1: duplicated)
   int32_t n_phases = 0;
   int64_t est = 0;                            // modelled time (cost units)
+  std::vector<std::vector<int64_t>> loads;    // per phase: each wave's load
 };
 
 // The clusters of one duplication threshold and subtree cap.
@@ -337,12 +341,13 @@ struct Clusters {
   std::vector<int64_t> path;                    // longest remaining path
 };
 
-Clusters clusters_of(const Graph& g, int64_t dup_max, int64_t cut_max) {
+Clusters clusters_of(const Graph& g, int64_t dup_max, int64_t cut_max, int neg_cost) {
   const int32_t n = (int32_t)g.nodes.size();
   auto sched = [&](int32_t v) {
     const int op = g.nodes[v].op;
     return op != XG_OP_CONST && op != XG_OP_INPUT;
   };
+  auto cost_of = [&](int32_t v) { return g.nodes[v].op == XG_OP_NEG ? neg_cost : op_cost(g.nodes[v].op); };
   std::vector<int32_t> nuse(n, 0), single(n, -1);
   std::vector<char> is_out(n, 0);
   for (auto& a : g.out) for (int32_t v : a) is_out[v] = 1;
@@ -362,7 +367,7 @@ Clusters clusters_of(const Graph& g, int64_t dup_max, int64_t cut_max) {
     if (!sched(v)) continue;
     int32_t ops[3];
     int k = operands(g, v, ops);
-    int64_t t = op_cost(g.nodes[v].op);
+    int64_t t = cost_of(v);
     for (int j = 0; j < k; ++j)
       if (sched(ops[j]) && nuse[ops[j]] == 1 && !cut[ops[j]]) t += tree[ops[j]];
     tree[v] = t;
@@ -383,7 +388,7 @@ Clusters clusters_of(const Graph& g, int64_t dup_max, int64_t cut_max) {
     clusters.push_back(r);
     bool has_out = false;
     for (int32_t v : members[r]) {
-      ccost[r] += op_cost(g.nodes[v].op);
+      ccost[r] += cost_of(v);
       has_out = has_out || is_out[v];
       int32_t ops[3];
       int k = operands(g, v, ops);
@@ -462,7 +467,11 @@ PhasedResult phased_schedule(const Graph& g, const Clusters& C, const std::vecto
   // entries that are out of date are skipped: a wide program has thousands of
   // clusters ready at once (a 30,000-operation DAG on 64 inputs plans in 2 s,
   // 30 when every choice looked at all of them).
-  auto rank = [&](int32_t r) { return policy.by_order ? -at[r] / W : C.path[r]; };
+  std::vector<std::vector<int32_t>> own(W, std::vector<int32_t>(policy.local ? n : 0, 0));  // operands by wave
+  auto rank = [&](int w, int32_t r) {
+    if (policy.local) return ((int64_t)own[w][r] << 40) + C.path[r];
+    return policy.by_order ? -at[r] / W : C.path[r];
+  };
   typedef std::pair<int64_t, int32_t> Entry;  // score, -cluster: the largest is taken
   std::vector<std::priority_queue<Entry>> ready(W);
   std::vector<std::vector<int64_t>> score(W, std::vector<int64_t>(n, 0));
@@ -483,7 +492,7 @@ PhasedResult phased_schedule(const Graph& g, const Clusters& C, const std::vecto
     return x;
   };
   auto enqueue = [&](int w, int32_t c) {
-    int64_t s = rank(c);
+    int64_t s = rank(w, c);
     if (policy.weight) {
       int64_t y = 0;
       for (int32_t d : cone[c])
@@ -557,7 +566,7 @@ PhasedResult phased_schedule(const Graph& g, const Clusters& C, const std::vecto
         load[w] += ccost[d];
         for (int32_t v : members[d]) { res.lists[w].push_back(v); res.phases[w].push_back(phase); }
       }
-      load[w] += ccost[r] + comm;
+      load[w] += ccost[r] + (policy.local ? 0 : comm);
       for (int32_t v : members[r]) {
         res.lists[w].push_back(v);
         res.phases[w].push_back(phase);
@@ -566,8 +575,10 @@ PhasedResult phased_schedule(const Graph& g, const Clusters& C, const std::vecto
       }
       held[w][r] = 1;
       newly.push_back({w, r});
-      for (int32_t s : esucc[r])
+      for (int32_t s : esucc[r]) {
+        if (policy.local) ++own[w][s];
         if (--miss[w][s] == 0 && !done[s]) enqueue(w, s);
+      }
     }
     if (newly.empty()) throw std::logic_error("phased plan: no cluster became ready");
     for (auto& wr : newly)
@@ -580,6 +591,7 @@ PhasedResult phased_schedule(const Graph& g, const Clusters& C, const std::vecto
     ++phase;
   }
   res.n_phases = phase;
+  res.loads = loads;
   // modelled time: per phase the slowest wave (its loads of other waves'
   // values are in its load already; its stores are added here) and a barrier
   std::vector<std::vector<int64_t>> stores(phase + 1, std::vector<int64_t>(W, 0));
@@ -743,6 +755,23 @@ static Plan phased_plan_of(const Graph& g, const PlanOptions& po, const Clusters
       seen[v] = 1;
     }
   }
+  if (policy.local) {
+    // one unit per exchanged value and reader, at the producer and at the
+    // reader, 30 per barrier; plans whose exchanges all fit the LDS come first
+    std::vector<std::vector<int64_t>> xfer(pl.n_phases + 1, std::vector<int64_t>(W, 0));
+    for (int w = 0; w < W; ++w)
+      for (int32_t k = 0; k <= pl.n_phases; ++k)
+        for (int32_t u : pl.mailbox[(size_t)w * (pl.n_phases + 1) + k]) {
+          xfer[k][w] += 1;
+          xfer[k - 1][r.owner[u]] += 1;
+        }
+    r.est = 8 * ws_loads / W + (pl.n_ws > 0 ? (int64_t)1 << 40 : 0);
+    for (int32_t k = 0; k < pl.n_phases; ++k) {
+      int64_t m = 0;
+      for (int w = 0; w < W; ++w) m = std::max(m, r.loads[k][w] + xfer[k][w]);
+      r.est += m + 30;
+    }
+  }
   pl.coop_est = r.est;
   pl.phase_len = (int32_t)T;
   return pl;
@@ -762,8 +791,20 @@ static Plan make_phased_plan(const Graph& g, const PlanOptions& po) {
   std::vector<Policy> policies = {Policy{false, 0}, Policy{false, 2}, Policy{true, 1}, Policy{true, 2}, Policy{true, 4}};
   if (po.transfers_first) policies = {Policy{false, 1000}};
   std::vector<std::pair<int64_t, int64_t>> shapes;  // duplication threshold, subtree cap
-  for (int64_t D : {1, 3})
-    for (int64_t S : {8, 16, 24, 48}) shapes.push_back({D, S});
+  // Programs with binary32 tags keep the scheduler that holds their values
+  // on the wave that made them, and what it counted a negation as (the
+  // compiler contracts their sums, so the graph does not show what a kernel
+  // issues).  Mixed MPC at 65,536 instances on 2 waves, two tiles on a CU:
+  // 528 us, with the other policies and their costs 645 at best.
+  const bool tagged = mixed_precision(g);
+  if (tagged) {
+    policies = {Policy{false, 0, true}};
+    for (int64_t D : {1, 2, 4, 8})
+      for (int64_t S : {0, 32, 96}) shapes.push_back({D, S});
+  } else {
+    for (int64_t D : {1, 3})
+      for (int64_t S : {8, 16, 24, 48}) shapes.push_back({D, S});
+  }
   struct Setting { int64_t T; size_t shape; Policy p; };
   std::vector<Setting> st;
   for (Policy p : policies)
@@ -800,7 +841,7 @@ static Plan make_phased_plan(const Graph& g, const PlanOptions& po) {
       if (err.empty()) err = e.what();
     }
   };
-  each(shapes.size(), [&](size_t k) { guarded([&]() { cl[k] = clusters_of(g, shapes[k].first, shapes[k].second); }); });
+  each(shapes.size(), [&](size_t k) { guarded([&]() { cl[k] = clusters_of(g, shapes[k].first, shapes[k].second, tagged ? 1 : op_cost(XG_OP_NEG)); }); });
   if (!err.empty()) throw std::logic_error(err);
   each(st.size(), [&](size_t i) {
     guarded([&]() {
