@@ -419,21 +419,24 @@ std::vector<Candidate> tune_candidates(xg_program* p, int64_t n, int mode) {
   // reverse sweep against the number of cuts (and levels of recomputation);
   // the fan-out trades states held per level against recomputation
   if (mode != 0) {
-    // (the pendulum's fused adjoint at 65,536 instances as one kernel: 245 us
-    // at 5/3 of the load setting, 255 with 500-operation leaves; fan-out 4
-    // takes 304, and budgets past twice the setting go to scratch, so they
-    // are not tried)
+    // (the pendulum's fused adjoint as one kernel, leaves of 150 operations at
+    // 4/3 of the load setting, fan-out 2 / 4: at 65,536 instances 245 / 263 us,
+    // at 16,384, where no spill leaves the LDS, 138 / 131; leaves of 250 at 5/3
+    // 250 / 290 and 148 / 153; budgets past twice the setting go to scratch)
+    auto leaves = [&](int rb, int sg, int fo) {
+      xg_options b = o;
+      b.reg_budget = rb;
+      b.adj_seg_ops = std::max(50, sg);
+      b.adj_fanout = fo;
+      // one kernel per adjoint for binary64 programs; binary32 ones keep
+      // their chunks (a single 68,000-statement binary32 kernel takes
+      // hiprtc minutes; the one-kernel candidate above stays)
+      if (one_kernel && p->g.dtype != XG_F32) b.chunk_ops = 5 * base.chunk_ops;
+      cands.push_back(b);
+    };
     for (int rb : {rb0 * 3 / 2, rb0 * 5 / 3, rb0 * 2})
-      for (int sg : {base.adj_seg_ops, base.adj_seg_ops * 2}) {
-        xg_options b = o;
-        b.reg_budget = rb;
-        b.adj_seg_ops = std::max(50, sg);
-        // one kernel per adjoint for binary64 programs; binary32 ones keep
-        // their chunks (a single 68,000-statement binary32 kernel takes
-        // hiprtc minutes; the one-kernel candidate above stays)
-        if (one_kernel && p->g.dtype != XG_F32) b.chunk_ops = 5 * base.chunk_ops;
-        cands.push_back(b);
-      }
+      for (int sg : {base.adj_seg_ops, base.adj_seg_ops * 2}) leaves(rb, sg, base.adj_fanout);
+    for (int fo : {2, 4}) leaves(rb0 * 4 / 3, base.adj_seg_ops * 3 / 5, fo);
   }
   // cooperative tiles, when few tiles leave SIMDs idle and the program is
   // wide (operations per dependency level) enough to split

@@ -30,3 +30,11 @@ def test_adjoint_candidates_hold_the_loaded_plans(mode, links, dtype, ns):
 def test_programs_with_options_have_no_library_candidate():
     p = xg.Program(configs.program_path("rdag200"), reg_budget=100, lds_slots=40)
     assert not any(library for _, library in plan_probe.candidates(p, 0, 1000))
+
+
+@pytest.mark.parametrize("fanout", [2, 4])
+def test_adjoint_candidates_vary_the_fanout(fanout):
+    """Short leaves with either fan-out: which is faster depends on the count."""
+    src = pendulum(4)
+    p = xg.Program(src, reg_budget=149, adj_seg_ops=150, adj_fanout=fanout, lds_slots=319)
+    assert plan_probe.code(p, 2, 16384)[0] in [h for h, _ in plan_probe.candidates(xg.Program(src), 2, 16384)]
