@@ -1060,17 +1060,27 @@ double width_of(const Graph& g) {
 // whole launch.  A program with few tiles (under 4 per CU) and at least
 // 32 x W operations per dependency level runs as W = B/64-wave cooperative
 // tiles, every other program on B-lane workgroups, one lane per instance.
-std::vector<std::pair<int, std::vector<xg_options>>> batch_candidates(xg_program* const* progs, int32_t k,
-                                                                      const int64_t* n) {
-  std::vector<std::pair<int, std::vector<xg_options>>> c;
+std::vector<std::pair<int, std::vector<Candidate>>> batch_candidates(xg_program* const* progs, int32_t k,
+                                                                     const int64_t* n) {
+  std::vector<std::pair<int, std::vector<Candidate>>> c;
   std::vector<double> width(k);
   for (int32_t i = 0; i < k; ++i) width[i] = width_of(progs[i]->g);
   for (int B : {64, 256, 512, 1024}) {
     const int W = B / 64;
-    std::vector<xg_options> os;
+    std::vector<Candidate> os;
     for (int32_t i = 0; i < k; ++i) {
       xg_options o = progs[i]->opt;
       const int64_t es = progs[i]->g.dtype == XG_F32 ? 4 : 8;
+      // The library's budgets are for one wave on a SIMD.  Two share its 512
+      // registers at 512 lanes and four at 1,024 (the MPC there, 2,048
+      // instances: 2,858 us with 112 values, 888 B of scratch per lane, 1,324
+      // with 48; 551 and 536 at 512 lanes with 112 and 96), and the lanes need
+      // the whole LDS.
+      const bool library = B == 64 && progs[i]->library_budget[0];
+      if (progs[i]->library_budget[0] && B > 64) {
+        o.reg_budget = progs[i]->g.dtype == XG_F32 ? (B >= 1024 ? 96 : kTuneRegs32) : (B >= 1024 ? 48 : kTuneRegs64);
+        o.lds_slots = (int32_t)(kLdsSpillBytes / (64 * es));
+      }
       o.ipt = 1;
       o.coop_phase = 0;  // (this autotuner does not try phased tiles; a program set to them runs so)
       if (W > 1 && (n[i] + 63) / 64 < 4 * 256 && width[i] >= 32.0 * W) {
@@ -1083,7 +1093,7 @@ std::vector<std::pair<int, std::vector<xg_options>>> batch_candidates(xg_program
         o.block = B;
         o.lds_slots = (int32_t)std::min<int64_t>(o.lds_slots, kLdsSpillBytes / (B * es));
       }
-      os.push_back(o);
+      os.emplace_back(o, library);
     }
     c.push_back({B, os});
   }
@@ -1092,12 +1102,12 @@ std::vector<std::pair<int, std::vector<xg_options>>> batch_candidates(xg_program
 
 // Trial copies of the programs with the candidate's options, and a batch
 // over them (source generated, not compiled); the batch owns the copies.
-xg_status batch_trial(xg_program* const* progs, int32_t k, const std::vector<xg_options>& os,
+xg_status batch_trial(xg_program* const* progs, int32_t k, const std::vector<Candidate>& os,
                       std::unique_ptr<xg_batch>& out) {
   std::vector<xg_program*> qs;
   for (int32_t i = 0; i < k; ++i) {
     std::string err;
-    if (!check_opts(os[i], progs[i]->g.dtype, err)) {
+    if (!check_opts(os[i].o, progs[i]->g.dtype, err)) {
       for (auto* q : qs) xg_program_free(q);
       set_error(err);
       return XG_EINVAL;
@@ -1120,6 +1130,24 @@ uint64_t batch_key(xg_program* const* progs, int32_t k, const int64_t* n) {
   }
   return h;
 }
+
+}  // namespace
+
+namespace xg {
+std::vector<std::pair<int, std::string>> batch_candidate_sources(xg_program* const* progs, int32_t k, const int64_t* n) {
+  std::vector<std::pair<int, std::string>> srcs;
+  for (auto& c : batch_candidates(progs, k, n)) {
+    std::unique_ptr<xg_batch> b;
+    if (batch_trial(progs, k, c.second, b) != XG_OK) continue;  // candidate not formable
+    srcs.push_back({c.first, b->src});
+    for (auto* q : b->owned) xg_program_free(q);
+    b->owned.clear();
+  }
+  return srcs;
+}
+}  // namespace xg
+
+namespace {
 
 size_t batch_ws_bytes(xg_batch* b, const int64_t* n) {
   size_t tot = kCounterBytes;
@@ -1153,13 +1181,7 @@ xg_status xg_batch_autotune_workspace_bytes(xg_program* const* progs, int32_t k,
 xg_status xg_batch_autotune_precompile(xg_program* const* progs, int32_t k, const int64_t* n) {
   if (!progs || k < 1 || !n) { set_error("bad argument"); return XG_EINVAL; }
   std::vector<std::string> srcs;
-  for (auto& c : batch_candidates(progs, k, n)) {
-    std::unique_ptr<xg_batch> b;
-    if (batch_trial(progs, k, c.second, b) != XG_OK) continue;
-    srcs.push_back(b->src);
-    for (auto* q : b->owned) xg_program_free(q);
-    b->owned.clear();
-  }
+  for (auto& c : batch_candidate_sources(progs, k, n)) srcs.push_back(std::move(c.second));
   std::vector<CodeObject> cos;
   std::string err;
   if (!compile_many(srcs, base_compile_options(progs[0]->opt.strict != 0), cos, err, progs[0]->opt.verbose != 0)) {

@@ -55,6 +55,16 @@ int probe_candidates(xg_program* p, int mode, long long n, unsigned long long* h
   return (int)cands.size();
 }
 
+// Workgroup sizes and sources (hashes) of the batch autotuner's candidates.
+int probe_batch_candidates(xg_program** ps, int k, const int64_t* n, int* block, unsigned long long* hash) {
+  int i = 0;
+  for (auto& c : xg::batch_candidate_sources(ps, k, n)) {
+    block[i] = c.first;
+    hash[i++] = xg::fnv1a(c.second, 1469598103934665603ull);
+  }
+  return i;
+}
+
 // Gives the plan for few tiles a source that does not compile.
 void probe_spoil_few(xg_program* p, int mode) {
   std::lock_guard<std::mutex> lk(p->mu);

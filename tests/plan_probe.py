@@ -63,3 +63,11 @@ def candidates(p, mode, n):
     k = lib().probe_candidates(p._h, mode, ctypes.c_longlong(n), h, l, 100)
     assert 0 < k <= 100
     return [(h[i], bool(l[i])) for i in range(k)]
+
+
+def batch_candidates(programs, ns):
+    """{workgroup size: hash of the source} of the batch autotuner's candidates."""
+    k = len(programs)
+    arr, na = (ctypes.c_void_p * k)(*[p._h.value for p in programs]), (ctypes.c_int64 * k)(*ns)
+    block, h = (ctypes.c_int * 8)(), (ctypes.c_ulonglong * 8)()
+    return {block[i]: h[i] for i in range(lib().probe_batch_candidates(arr, k, na, block, h))}

@@ -36,3 +36,26 @@ def test_batch_workspace_is_the_plans(tmp_path, keys):
         used, have = accesses(plan_probe.batch_source([p], str(tmp_path / "b.hip")), 4 if p.dtype == "f32" else 8)
         assert have == p.info(0)["n_ws_slots"] * 64 * (4 if p.dtype == "f32" else 8)
         assert used < max(have, 1)
+
+
+def test_wide_workgroups_have_the_budgets_of_theirs():
+    """The library's budgets are those of one wave on a SIMD: batch candidates
+    of more lanes hold fewer values each, and 64 lanes run as loaded."""
+    keys, ns = ("rdag1e4", "ldl48"), (512, 4000)
+    own = {b: [xg.Program(configs.program_path(k), **o) for k, o in zip(keys, os)] for b, os in
+           ((512, (dict(reg_budget=200, lds_slots=638), dict(reg_budget=112, lds_slots=319))),
+            (1024, (dict(reg_budget=96, lds_slots=638), dict(reg_budget=48, lds_slots=319))))}
+    a = plan_probe.batch_candidates([xg.Program(configs.program_path(k)) for k in keys], ns)
+    b, c = (plan_probe.batch_candidates(own[w], ns) for w in (512, 1024))
+    assert sorted(a) == [64, 256, 512, 1024]
+    assert a[256] == b[256] and a[512] == b[512] and a[1024] == c[1024]
+    assert a[64] != b[64]
+
+
+def test_64_lanes_run_as_loaded(tmp_path):
+    ps = [xg.Program(configs.program_path(k)) for k in ("rdag1e3", "ldl48")]
+    src = plan_probe.batch_source(ps, str(tmp_path / "b.hip"))
+    h = 1469598103934665603
+    for c in src.encode():
+        h = (h ^ c) * 1099511628211 & (1 << 64) - 1
+    assert plan_probe.batch_candidates(ps, (65536, 4000))[64] == h
