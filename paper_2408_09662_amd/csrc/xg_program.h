@@ -128,6 +128,9 @@ bool plan_candidates(xg_program* p, int64_t n, int mode, std::vector<Candidate>&
                      std::vector<std::unique_ptr<xg_program>>& trials, std::string& err);
 // The source of the persistent kernel over progs (host only: nothing is compiled)
 xg_status batch_source(const std::vector<xg_program*>& progs, std::string& src);
+// Workgroups of a batch launch of tiles[k] tiles of cost[k] each, of which
+// `resident` fit the chip's `cus` CUs at once
+int64_t batch_grid(const std::vector<int64_t>& tiles, const std::vector<int64_t>& cost, int64_t resident, int64_t cus);
 // The workgroup sizes xg_batch_autotune tries for n[i] instances of program i, and the sources
 std::vector<std::pair<int, std::string>> batch_candidate_sources(xg_program* const* progs, int32_t k, const int64_t* n);
 void reset_mode(xg_program* p, int mode);  // drain, unload, forget the plan

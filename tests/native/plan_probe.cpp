@@ -65,6 +65,11 @@ int probe_batch_candidates(xg_program** ps, int k, const int64_t* n, int* block,
   return i;
 }
 
+// Workgroups of a batch launch.
+long long probe_batch_grid(int k, const int64_t* tiles, const int64_t* cost, long long resident, long long cus) {
+  return xg::batch_grid({tiles, tiles + k}, {cost, cost + k}, resident, cus);
+}
+
 // Gives the plan for few tiles a source that does not compile.
 void probe_spoil_few(xg_program* p, int mode) {
   std::lock_guard<std::mutex> lk(p->mu);

@@ -71,3 +71,11 @@ def batch_candidates(programs, ns):
     arr, na = (ctypes.c_void_p * k)(*[p._h.value for p in programs]), (ctypes.c_int64 * k)(*ns)
     block, h = (ctypes.c_int * 8)(), (ctypes.c_ulonglong * 8)()
     return {block[i]: h[i] for i in range(lib().probe_batch_candidates(arr, k, na, block, h))}
+
+
+def batch_grid(tiles, cost, resident, cus):
+    k = len(tiles)
+    f = lib().probe_batch_grid
+    f.restype = ctypes.c_longlong
+    return f(k, (ctypes.c_int64 * k)(*tiles), (ctypes.c_int64 * k)(*cost), ctypes.c_longlong(resident),
+             ctypes.c_longlong(cus))

@@ -59,3 +59,14 @@ def test_64_lanes_run_as_loaded(tmp_path):
     for c in src.encode():
         h = (h ^ c) * 1099511628211 & (1 << 64) - 1
     assert plan_probe.batch_candidates(ps, (65536, 4000))[64] == h
+
+
+@pytest.mark.parametrize("tiles,cost,grid", [
+    ([1024, 128, 8, 32], [1500, 15000, 150000, 50000], 256),  # the 8 long tiles bound the launch
+    ([1024, 128, 8], [1500, 5000, 4500], 1024),               # the many short ones do
+    ([3, 0], [100, 10 ** 9], 3),                              # an empty program's tiles cost nothing
+    ([128], [7], 128), ([257], [7], 257), ([5000], [7], 1024),
+])
+def test_workgroups_of_a_launch(tiles, cost, grid):
+    assert plan_probe.batch_grid(tiles, cost, 1024, 256) == grid
+    assert plan_probe.batch_grid(tiles, cost, 64, 256) == min(grid, 64)
