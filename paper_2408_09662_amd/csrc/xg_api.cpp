@@ -464,7 +464,8 @@ bool load_plans(xg_program* p, int mode, std::string& err, xg_status* code) {
 
 bool load_for(xg_program* p, int mode, int64_t n, void* stream, bool& few, std::string& err, xg_status* code) {
   few = pick_few(p, mode, n);
-  if (!few || devmod(p->few[mode])) return compile_mode(p, mode, err, code, few);
+  if (!few) return compile_mode(p, mode, err, code);
+  if (devmod(p->few[mode])) return true;
   // The plan that fills the chip is loaded before or with the one for few
   // tiles, so after one evaluation of any count a capturing stream finds
   // code for every count; it loads no module.
