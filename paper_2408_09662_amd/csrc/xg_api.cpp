@@ -102,6 +102,16 @@ static int64_t tile_cost(const ModeState& M) {
   return (c + 2 * M.est.lds_ops + 4 * M.est.ws_ops) * 4 / 3;
 }
 
+// What a choice between phased plans compares.  A plan's spills add to its
+// modelled time, workspace accesses most of all: an LDL^T solve of 48 x 48 at
+// 10,000 instances takes 247 us with 32,600 + 16,195 accesses on 4 waves, 171
+// with 35,500 + 8,451; the MPC on 2 waves 125 us at 4,096 instances and 565 at
+// 65,536 with 77,900 + 4,709, 111 and 536 with 79,500 + 4,318, 132 and 649
+// with 77,200 + 6,015.  LDS accesses weigh little (at 2 each the quadcopter's
+// 22,730 + 8,288 on 4 waves lose to 28,234 + 3,900 on 2: 20 steps of 10,000
+// instances 805 us against 1,042).
+static int64_t spill_score(const Plan& pl, const EmitStats& st) { return pl.coop_est + 12 * st.ws_ops + st.lds_ops / 2; }
+
 bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
   ModeState& M = mode_state(p, mode, few);
   if (M.planned) return true;
@@ -183,6 +193,21 @@ bool plan_mode(xg_program* p, int mode, std::string& err, bool few) {
   if (M.plan.phased) M.srcs = emit_phased(M.g, M.plan, eo, prefix, &M.est);
   else if (M.plan.waves > 1) M.srcs = emit_wide(M.g, M.plan, eo, prefix, &M.est);
   else M.srcs = emit_chunks(M.g, M.plan, eo, prefix, &M.est, M.plan.n_ws);
+  if (M.plan.phased && !p->library_budget[0] && !po.transfers_first && M.est.ws_ops > 0 && !mixed_precision(M.g)) {
+    // phased tiles the caller asks for that spill to the workspace: ranked by
+    // transfers too (form_few does so for the library's; 48 x 48 LDL^T solve,
+    // 10,000 instances, 2 waves: 468 us ranked by path or order, 176 so, 195
+    // when operands computed on the wave came first)
+    po.transfers_first = true;
+    Plan pl = make_plan(M.g, po);
+    EmitStats st;
+    std::vector<std::string> srcs = emit_phased(M.g, pl, eo, prefix, &st);
+    if (spill_score(pl, st) < spill_score(M.plan, M.est)) {
+      M.plan = std::move(pl);
+      M.est = st;
+      M.srcs.swap(srcs);
+    }
+  }
   if (opt.verbose)
     std::fprintf(stderr,
                  "[xg] mode %d: %zu nodes, %lld ops, max live %lld, %zu chunks, ws %d+%d slots, "
@@ -250,14 +275,6 @@ static void form_few(xg_program* p, int mode) {
   ModeState best;
   xg_options best_o = o;
   bool best_first = false;
-  // A plan's spills add to its modelled time, workspace accesses most of all:
-  // an LDL^T solve of 48 x 48 at 10,000 instances takes 247 us with 32,600 +
-  // 16,195 accesses on 4 waves, 171 with 35,500 + 8,451; the MPC on 2 waves
-  // 125 us at 4,096 instances and 565 at 65,536 with 77,900 + 4,709, 111 and
-  // 536 with 79,500 + 4,318, 132 and 649 with 77,200 + 6,015.  LDS accesses
-  // weigh little (at 2 each the quadcopter's 22,730 + 8,288 on 4 waves lose to
-  // 28,234 + 3,900 on 2: 20 steps of 10,000 instances 805 us against 1,042).
-  auto score = [](const ModeState& M) { return M.plan.coop_est + 12 * M.est.ws_ops + M.est.lds_ops / 2; };
   auto consider = [&](int W, int phase, bool transfers_first) {
     o.waves = W;
     o.coop_phase = phase;
@@ -266,7 +283,7 @@ static void form_few(xg_program* p, int mode) {
     p->few_transfers_first = transfers_first;
     p->few_opt[0] = o;
     if (!plan_mode(p, 0, err, true)) return;
-    if (!best.planned || score(p->few[0]) < score(best)) {
+    if (!best.planned || spill_score(p->few[0].plan, p->few[0].est) < spill_score(best.plan, best.est)) {
       best = std::move(p->few[0]);
       best_o = o;
       best_o.coop_phase = best.plan.phase_len;
