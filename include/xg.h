@@ -185,7 +185,9 @@ xg_status xg_program_load(const xg_program_desc* desc, const xg_options* opts,
  * that hold them to finish queued work (launches are asynchronous). */
 void xg_program_free(xg_program* p);
 
-/* mode: 0 forward, 1 adjoint (gradient), 2 fused forward + adjoint. */
+/* mode: 0 forward, 1 adjoint (gradient), 2 fused forward + adjoint.  Where
+ * the library plans a mode twice, this and xg_program_options describe the
+ * plan that fills the chip. */
 xg_status xg_program_info(xg_program* p, int32_t mode, xg_info* info);
 
 /* The options `mode` is planned and launched with (library defaults
